@@ -149,9 +149,12 @@ bool fusable(const kq_layer* layers, int32_t l0, int32_t l1) {
 // (assign_partition), which split its units evenly; a layer's fused partials are those of
 // its workgroups.  For every layer: its first workgroup and their number; returns the grid.
 int fused_slots(const kq_layer* layers, int32_t l0, int32_t l1, int* wfirst, int* nslots) {
-    int units[KQ_MAX_STACK];
-    for (int32_t l = l0; l < l1; ++l) units[l - l0] = assign_units(layers[l].n);
-    const int grid = assign_partition(units, l1 - l0, nslots);
+    int units[KQ_MAX_STACK], ks[KQ_MAX_STACK];
+    for (int32_t l = l0; l < l1; ++l) {
+        units[l - l0] = assign_units(layers[l].n);
+        ks[l - l0] = layers[l].k;
+    }
+    const int grid = assign_partition(units, ks, l1 - l0, nslots);
     int w = 0;
     for (int32_t l = 0; l < l1 - l0; ++l) {
         wfirst[l] = w;

@@ -36,9 +36,10 @@
 // score of a farther entry may overflow to +inf or NaN, which the slot minima skip.
 //
 // Grid.  Kernels are cut into units of 64 (one kernel per lane of a wave).  The grid of
-// at most kAssignGridMax workgroups is split per layer: layer l gets ceil(U_l / t)
-// workgroups, t the smallest unit count per workgroup for which the total fits, and its
-// U_l units are spread evenly over them, so a workgroup works within one layer; its waves
+// at most kAssignGridMax workgroups is split per layer by cost (assign_partition): layer l
+// gets ceil(U_l / floor(t / w_l)) workgroups, w_l the cost of one of its units and t the
+// smallest cost per workgroup for which the total fits, and its U_l units are spread
+// evenly over them, so a workgroup works within one layer; its waves
 // take consecutive units round by round.  A codebook of up to kAssignChunk entries is
 // split and staged once in LDS, in the MFMA A-operand
 // order [tile][k-step][lane][8 x bf16] (one conflict-free ds_read_b128 per MFMA
@@ -601,21 +602,30 @@ __global__ __launch_bounds__(kSumThreads) void assign_finish_kernel(const StackP
 }
 
 
-int assign_partition(const int* units, int nlayers, int* g) {
-    long long T = 0;
-    int umax = 1;
+// A unit costs about kUnitCost + kpad entries' time: the scan grows with the codebook, the split,
+// the rescoring, the guard and the outputs do not (on the 16-layer ResNet-18 stack a fused launch
+// takes 22 us at k = 16 and 34 us at k = 256: 17 us without the start-up, and 12 us for 240
+// entries).  With units counted alike, the layers with the largest codebooks ended last: the
+// VGG-16 stack with k = 60 .. 1088 took 150 us per launch, with the cost 101 us; the ResNet-18
+// stack with k = 609 .. 7679 688 and 568 us.
+constexpr long long kUnitCost = 320;
+
+int assign_partition(const int* units, const int* ks, int nlayers, int* g) {
+    long long w[KQ_MAX_STACK], lo = 1, hi = 1;
     for (int l = 0; l < nlayers; ++l) {
-        T += units[l];
-        umax = units[l] > umax ? units[l] : umax;
+        w[l] = kUnitCost + ((ks[l] + 63) & ~63);
+        lo = w[l] > lo ? w[l] : lo;
+        hi = units[l] * w[l] > hi ? units[l] * w[l] : hi;
     }
-    auto count = [&](long long t) {
+    auto count = [&](long long t) {  // workgroups when each takes at most t, t >= every w
         long long c = 0;
-        for (int l = 0; l < nlayers; ++l) c += (units[l] + t - 1) / t;
+        for (int l = 0; l < nlayers; ++l) {
+            const long long m = t / w[l];
+            c += (units[l] + m - 1) / m;
+        }
         return c;
     };
-    long long lo = (T + kAssignGridMax - 1) / kAssignGridMax, hi = umax;  // count(hi) = nlayers <= the grid
-    if (lo < 1) lo = 1;
-    while (lo < hi) {
+    while (lo < hi) {  // count(hi) = nlayers <= the grid
         const long long mid = (lo + hi) / 2;
         if (count(mid) <= kAssignGridMax)
             hi = mid;
@@ -624,7 +634,8 @@ int assign_partition(const int* units, int nlayers, int* g) {
     }
     int grid = 0;
     for (int l = 0; l < nlayers; ++l) {
-        g[l] = (int)((units[l] + lo - 1) / lo);
+        const long long m = lo / w[l];
+        g[l] = (int)((units[l] + m - 1) / m);
         grid += g[l];
     }
     return grid;

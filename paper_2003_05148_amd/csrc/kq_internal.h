@@ -282,8 +282,9 @@ constexpr int kSumThreads = 640;
 
 // launchers (return hipSuccess or the launch error)
 // the assignment's workgroups per layer (every workgroup works on one layer): g[l] =
-// ceil(units_l / t) for the smallest t with sum g[l] <= kAssignGridMax; returns the grid
-int assign_partition(const int* units, int nlayers, int* g);
+// ceil(units_l / floor(t / w_l)), w_l the cost of a unit of layer l (it grows with its codebook),
+// for the smallest t with sum g[l] <= kAssignGridMax; returns the grid
+int assign_partition(const int* units, const int* ks, int nlayers, int* g);
 hipError_t launch_assign(const StackParams& p, hipStream_t s, bool fused = false, hipEvent_t start = nullptr,
                          hipEvent_t stop = nullptr);
 hipError_t launch_assign_finish(const StackParams& p, hipStream_t s);
