@@ -1103,6 +1103,8 @@ __global__ __launch_bounds__(kFcThreads) void fc_assign_kernel(const FcParams p)
                     cw[j] = (!INIT && g < ng) ? c4[g] : 0u;
                 }
             };
+            // the loop runs for the whole wave while its first lane has a group: the queue's count
+            // must stay the same in every lane, and a drain needs all of them
             long long g0 = (long long)blockIdx.x * kFcThreads * kGPer + tid;
             // kDepth steps in flight: this one and the next (a sweep of groups per step and
             // depth kept 2 and 2)
@@ -1111,9 +1113,9 @@ __global__ __launch_bounds__(kFcThreads) void fc_assign_kernel(const FcParams p)
             unsigned cb[kDepth][kGPer];
 #pragma unroll
             for (int d = 0; d < kDepth - 1; ++d)
-                if (g0 + d * step < ng) load(g0 + d * step, xb[d], cb[d]);
-            for (; g0 < ng; g0 += step) {
-                if (g0 + (kDepth - 1) * step < ng) load(g0 + (kDepth - 1) * step, xb[kDepth - 1], cb[kDepth - 1]);
+                if (g0 - ln + d * step < ng) load(g0 + d * step, xb[d], cb[d]);
+            for (; g0 - ln < ng; g0 += step) {
+                if (g0 - ln + (kDepth - 1) * step < ng) load(g0 + (kDepth - 1) * step, xb[kDepth - 1], cb[kDepth - 1]);
                 float4 (&xv)[kGPer] = xb[0];
                 unsigned (&cw)[kGPer] = cb[0];
                 float xs[kGPer][4];

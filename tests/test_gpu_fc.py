@@ -121,3 +121,19 @@ def test_fc_threshold_path_equals_the_exact_search(kind):
     b = kq.kq_quantize_scalars(vd, 6, 30, search="exact")
     for x, y, name in zip(a, b, ["codes", "levels", "v_hat", "rounds"]):
         assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), (kind, name)
+
+
+@pytest.mark.parametrize("groups", [1, 5, 63, 65, 129, 600, 512 * 1024 + 7])
+def test_fc_threshold_rounds_with_a_partial_last_wave(groups):
+    """Sets whose last wave holds fewer than 64 groups of four scalars, with many codes changing
+    there: every change must move its level's sums (the count of a wave's queued changes has to
+    agree in all its lanes, also in those past the end)."""
+    m = 4 * groups
+    v = data("heavy", m, groups)
+    v[-min(m, 256):] = np.random.default_rng(1).uniform(-0.02, 0.02, min(m, 256)).astype(np.float32)
+    vd = dev(v)
+    for iters in (1, 2, 3, 30):
+        a = kq.kq_quantize_scalars(vd, 6, iters, search="thresholds")
+        b = kq.kq_quantize_scalars(vd, 6, iters, search="exact")
+        for x, y, name in zip(a, b, ["codes", "levels", "v_hat", "rounds"]):
+            assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), (groups, iters, name)
