@@ -239,9 +239,9 @@ kq_status kq_codebook_grad_step_stack(const kq_layer* layers, int32_t n_layers, 
  *   3 * 2^20 scalars on each round first finds, per level boundary, the smallest value that
  *   takes the next code (a search over fp32 values with the exact search, started at the
  *   midpoint of the two levels) and then codes
- *   every scalar with fp32 comparisons only.  This is used only where every fp64 distance
- *   between a data value and a level is exact (no nonzero value or level below 2^-29 of the
- *   largest magnitude), so it gives the exact search's codes; KQ_F_EXACT_SEARCH /
+ *   every scalar with fp32 comparisons only.  This is used only where distinct neighbouring
+ *   levels are at least 2^-50 of the largest magnitude apart, so that rounding a distance to
+ *   fp64 cannot reorder it, and gives the exact search's codes; KQ_F_EXACT_SEARCH /
  *   KQ_F_THRESHOLDS force one way (flags 0 = the size rule).
  *   v device [count] fp32 (finite); codes device [count] uint8; levels device [2^bits] fp32;
  *   v_hat device [count] (= levels[codes], may be NULL); rounds device int32 (level updates

@@ -194,10 +194,17 @@ __device__ __forceinline__ int nearest_sorted_fast(float x, const float* s_lev, 
     return q;
 }
 
-// Code thresholds.  With sorted levels the code of v (nearest level, lowest index on
-// ties, fp64 distances) never decreases as v grows: the distance to a lower level only
-// grows and to a higher one only shrinks.  So code(v) = the number of q < nlev - 1 with
-// t_q <= v, where t_q is the smallest fp32 value whose code exceeds q (+inf if none).
+// Code thresholds.  With sorted levels whose distinct neighbours are at least 2^-50 M apart (M
+// the largest magnitude of the data, so of the levels too) the code of v (nearest level, lowest
+// index on ties, distances rounded to fp64) never decreases as v grows, for any v in the data
+// range.  Let fl be the rounding, which is monotone, v < v', and suppose code(v) = q and
+// code(v') = q' < q (so L_q' < L_q).  fl|v - L_q| < fl|v - L_q'| (a tie would take q'), so v, and
+// with it v', lies above the middle of the two.  If v' <= L_q, then fl(L_q - v') <= fl(L_q - v) <
+// fl(v - L_q') <= fl(v' - L_q'): q' cannot win at v'.  If v' > L_q, the two distances differ by
+// L_q - L_q' >= 2^-50 M, at least two units in the last place of numbers up to 2 M: their
+// roundings keep the order, and again q' cannot win.  So code(v) = the number of q < nlev - 1
+// with t_q <= v, where t_q is the smallest fp32 value whose code exceeds q (+inf if none).  By the
+// same margin no level but a neighbour of v can tie with it, so nearest_sorted finds the code.
 // t_q is found by bisection over the fp32 values in their order, evaluating code() with
 // nearest_sorted; afterwards each scalar needs only fp32 comparisons.
 __device__ __forceinline__ unsigned ordered_key(float f) {
@@ -207,10 +214,7 @@ __device__ __forceinline__ unsigned ordered_key(float f) {
 __device__ __forceinline__ float key_value(unsigned k) {
     return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
-// Searched within the data range [vmin, vmax] only, and used only where every fp64
-// distance |v - L| there is exact (see exact_floor): rounding could otherwise make
-// distances to distinct levels equal for far values and send them to a lower index.
-// The boundary lies next to the midpoint of levels q and q + 1, so the search starts there:
+// Searched within the data range [vmin, vmax] only.  The boundary lies next to the midpoint of levels q and q + 1, so the search starts there:
 // it steps away from the midpoint by 1, 2, 4, ... keys until the code crosses q, then
 // bisects the last step.  Every probe keeps code(lo) <= q < code(hi), and the code does not
 // decrease with the value, so the answer is the same as bisecting [vmin, vmax] from the
@@ -760,15 +764,14 @@ __host__ __device__ __forceinline__ bool fc_thr_wanted(const FcParams& p) {
 
 __device__ __forceinline__ bool fc_done(const FcParams& p) { return p.state[0] != 0; }
 
-// per workgroup: min, max and smallest nonzero magnitude of its scalars
+// per workgroup: min and max of its scalars
 __global__ __launch_bounds__(kFcThreads) void fc_minmax_kernel(const FcParams p) {
-    __shared__ float s_lo[kFcThreads / kWave], s_hi[kFcThreads / kWave], s_sm[kFcThreads / kWave];
+    __shared__ float s_lo[kFcThreads / kWave], s_hi[kFcThreads / kWave];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    float lo = __builtin_inff(), hi = -__builtin_inff(), sm = __builtin_inff();
+    float lo = __builtin_inff(), hi = -__builtin_inff();
     auto take = [&](float x) {
         lo = fminf(lo, x);
         hi = fmaxf(hi, x);
-        if (x != 0.0f) sm = fminf(sm, fabsf(x));
     };
     long long r0 = 0;  // scalars from here on: one at a time
     if ((reinterpret_cast<uintptr_t>(p.v) & 15u) == 0) {  // float4 groups, four per thread in flight
@@ -800,23 +803,19 @@ __global__ __launch_bounds__(kFcThreads) void fc_minmax_kernel(const FcParams p)
     for (int off = 32; off >= 1; off >>= 1) {
         lo = fminf(lo, __shfl_xor(lo, off));
         hi = fmaxf(hi, __shfl_xor(hi, off));
-        sm = fminf(sm, __shfl_xor(sm, off));
     }
     if (lane == 0) {
         s_lo[wave] = lo;
         s_hi[wave] = hi;
-        s_sm[wave] = sm;
     }
     __syncthreads();
     if (tid == 0) {
         for (int w = 1; w < kFcThreads / kWave; ++w) {
             lo = fminf(lo, s_lo[w]);
             hi = fmaxf(hi, s_hi[w]);
-            sm = fminf(sm, s_sm[w]);
         }
-        p.minmax[3 * blockIdx.x] = lo;
-        p.minmax[3 * blockIdx.x + 1] = hi;
-        p.minmax[3 * blockIdx.x + 2] = sm;
+        p.minmax[2 * blockIdx.x] = lo;
+        p.minmax[2 * blockIdx.x + 1] = hi;
     }
 }
 
@@ -828,22 +827,24 @@ __device__ __forceinline__ int fc_bucket(float x, float lo, float sc) {
     return (int)fminf(fmaxf(t, 0.0f), (float)(kFcBuckets - 1));
 }
 
-// thresholds of the levels s_lev (sorted unless s_unsorted) when every distance from the
-// data range to them is exact in fp64 (state[3]); otherwise state[3] = 0 and the codes
-// are found by the exact search.  With thresholds and a finite bucket scale the bucket
+// thresholds of the levels s_lev (sorted unless s_unsorted) when distinct neighbours are at
+// least 2^-50 of the largest magnitude apart (state[3]); otherwise state[3] = 0 and the codes
+// are found by the exact search.  (An earlier rule asked for exact fp64 distances: no nonzero
+// value or level below 2^-29 of the largest magnitude.  Every second set of 10^8 normal values
+// holds a smaller one, and its rounds took 520 us by the exact search instead of 104.)  With thresholds and a finite bucket scale the bucket
 // table follows: for bucket b, c = the number of thresholds whose bucket is below b (all
 // of them below every value of b) and n = the number inside b; entry b = (c | n << 8,
 // threshold c or +inf).  A value's code is then c plus the count of the n thresholds
 // c .. c + n - 1 at or below it.  Every thread of the workgroup calls it.
 __device__ void set_thresholds(const FcParams& p, const float* s_lev, int nlev, int unsorted, int* s_bad, float vmin,
-                               float vmax, float vsm) {
+                               float vmax) {
     const int tid = threadIdx.x;
-    const float fl = exact_floor(fmaxf(fabsf(vmin), fabsf(vmax)));
+    const double apart = 0x1p-50 * (double)fmaxf(fabsf(vmin), fabsf(vmax));
     // the boundary search costs a few microseconds per round: worth it only for large sets
     const bool wanted = fc_thr_wanted(p);
-    if (tid == 0) *s_bad = (unsorted || vsm < fl || !wanted) ? 1 : 0;
+    if (tid == 0) *s_bad = (unsorted || !wanted) ? 1 : 0;
     __syncthreads();
-    if (tid < nlev && s_lev[tid] != 0.0f && fabsf(s_lev[tid]) < fl) *s_bad = 1;
+    if (tid + 1 < nlev && s_lev[tid] != s_lev[tid + 1] && (double)s_lev[tid + 1] - (double)s_lev[tid] < apart) *s_bad = 1;
     __syncthreads();
     const int ok = *s_bad == 0;
     float t = __builtin_inff();
@@ -896,44 +897,38 @@ __device__ void set_thresholds(const FcParams& p, const float* s_lev, int nlev, 
 
 // the uniform grid on [min, max]; clears the run state and the running sums
 __global__ __launch_bounds__(kCbqMaxLevels) void fc_grid_kernel(const FcParams p, int nblk) {
-    __shared__ float s_lo, s_hi, s_sm;
+    __shared__ float s_lo, s_hi;
     __shared__ float s_lev[kCbqMaxLevels];
     __shared__ int s_unsorted, s_bad;
-    __shared__ float s_w[3][kCbqMaxLevels / kWave];
+    __shared__ float s_w[2][kCbqMaxLevels / kWave];
     const int tid = threadIdx.x, nlev = 1 << p.bits;
     {  // the workgroups' minima and maxima: strided per thread, then across the wave and the waves
-        float lo = __builtin_inff(), hi = -__builtin_inff(), sm = __builtin_inff();
+        float lo = __builtin_inff(), hi = -__builtin_inff();
         for (int b = tid; b < nblk; b += kCbqMaxLevels) {
-            lo = fminf(lo, p.minmax[3 * b]);
-            hi = fmaxf(hi, p.minmax[3 * b + 1]);
-            sm = fminf(sm, p.minmax[3 * b + 2]);
+            lo = fminf(lo, p.minmax[2 * b]);
+            hi = fmaxf(hi, p.minmax[2 * b + 1]);
         }
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) {
             lo = fminf(lo, __shfl_xor(lo, off));
             hi = fmaxf(hi, __shfl_xor(hi, off));
-            sm = fminf(sm, __shfl_xor(sm, off));
         }
         if ((tid & (kWave - 1)) == 0) {
             s_w[0][tid / kWave] = lo;
             s_w[1][tid / kWave] = hi;
-            s_w[2][tid / kWave] = sm;
         }
     }
     __syncthreads();
     if (tid == 0) {
-        float lo = s_w[0][0], hi = s_w[1][0], sm = s_w[2][0];
+        float lo = s_w[0][0], hi = s_w[1][0];
         for (int w = 1; w < kCbqMaxLevels / kWave; ++w) {
             lo = fminf(lo, s_w[0][w]);
             hi = fmaxf(hi, s_w[1][w]);
-            sm = fminf(sm, s_w[2][w]);
         }
         s_lo = lo;
         s_hi = hi;
-        s_sm = sm;
         p.range[0] = lo;
         p.range[1] = hi;
-        p.range[2] = sm;
         s_unsorted = 0;
         p.state[0] = 0;  // not converged
         p.state[1] = 0;  // level updates made
@@ -949,7 +944,7 @@ __global__ __launch_bounds__(kCbqMaxLevels) void fc_grid_kernel(const FcParams p
     if (tid + 1 < nlev && !(s_lev[tid] <= s_lev[tid + 1])) s_unsorted = 1;
     __syncthreads();
     if (tid == 0) p.state[2] = s_unsorted;
-    set_thresholds(p, s_lev, nlev, s_unsorted, &s_bad, s_lo, s_hi, s_sm);
+    set_thresholds(p, s_lev, nlev, s_unsorted, &s_bad, s_lo, s_hi);
 }
 
 // Each thread takes four scalars per step (r0 + 256 j, consecutive lanes consecutive
@@ -1348,7 +1343,7 @@ __global__ __launch_bounds__(kCbqMaxLevels) void fc_state_kernel(const FcParams 
     __syncthreads();
     if (update && tid + 1 < nlev && !(s_lev[tid] <= s_lev[tid + 1])) s_unsorted = 1;
     __syncthreads();
-    if (update) set_thresholds(p, s_lev, nlev, s_unsorted, &s_bad, p.range[0], p.range[1], p.range[2]);  // uniform
+    if (update) set_thresholds(p, s_lev, nlev, s_unsorted, &s_bad, p.range[0], p.range[1]);  // uniform
     if (tid == 0) {
         if (update) {
             p.state[1] += 1;

@@ -325,8 +325,8 @@ struct FcParams {
     long long m;
     int bits, iters;
     int thr_mode;          // codes from thresholds: 0 from 2^23 scalars on, 1 never, 2 whenever valid
-    float* minmax;         // [grid][3] per-workgroup min, max, smallest nonzero magnitude
-    float* range;          // [4] the data's min, max, smallest nonzero magnitude; the bucket scale
+    float* minmax;         // [grid][2] per-workgroup min, max
+    float* range;          // [4] the data's min, max; -; the bucket scale
     long long* part;       // [grid][levels][12] per-workgroup digits and counts
     long long* S;          // [levels][12] running exact sums and counts
     float* lev;            // [levels] current levels

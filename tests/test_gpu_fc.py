@@ -123,6 +123,22 @@ def test_fc_threshold_path_equals_the_exact_search(kind):
         assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), (kind, name)
 
 
+@pytest.mark.parametrize("bits", [1, 2, 3, 6])
+@pytest.mark.parametrize("m", [64, 5001])
+def test_fc_thresholds_with_values_far_below_the_levels(m, bits):
+    """Values down to the smallest subnormal between levels that lie symmetrically around zero:
+    their fp64 distances to both levels round to the same number, and the tie goes to the
+    lower level; the thresholds (and the exact search) must code them alike."""
+    rng = np.random.default_rng(m + bits)
+    v = rng.choice([-0.5, -0.25, 0.25, 0.5], m).astype(np.float32)
+    tiny = rng.random(m) < 0.4
+    e = rng.uniform(-45.0, -9.0, int(tiny.sum()))
+    v[tiny] = (rng.choice([-1.0, 1.0], e.size) * 10.0 ** e).astype(np.float32)
+    v[:4] = [0.0, -0.0, 1e-45, -1e-45]
+    check(v, bits, 30, f"m={m} bits={bits}")
+    check(np.concatenate([v, -v]), bits, 30, f"symmetric m={m} bits={bits}")
+
+
 @pytest.mark.parametrize("groups", [1, 5, 63, 65, 129, 600, 512 * 1024 + 7])
 def test_fc_threshold_rounds_with_a_partial_last_wave(groups):
     """Sets whose last wave holds fewer than 64 groups of four scalars, with many codes changing
