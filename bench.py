@@ -314,10 +314,13 @@ def main():
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / FP32_PEAK_TFLOPS,
                      "traffic": assign_traffic() if (args.config, k) == ("resnet18", 256) else None,
-                     "kernel": ("assign_kernel<2, true> (member sums fused)" if fused else "assign_kernel<2, false>")
+                     "kernel": ("assign_kernel<true, 256> (member sums fused)" if fused else
+                                "assign_kernel<false, 1024>" if max(L.k for L in layers) <= 1024 else
+                                "assign_large_kernel")
                                + f": one Lloyd round's launch per timed step (rounds 0..{min(args.steps, T) - 1}), "
                                  "whole stack per launch",
-                     "pricing": "bf16-split MFMA screening + exact fp32 rescoring; the method's fp32 flops "
+                     "pricing": "bf16-split (one fp16 product above 1024 entries) MFMA screening + exact fp32 "
+                                "rescoring; the method's fp32 flops "
                                 "(18 k per kernel) priced at the 157.3 TFLOP/s FP32 peak"},
     }
     if not args.no_cpu_baseline:

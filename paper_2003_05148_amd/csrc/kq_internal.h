@@ -15,17 +15,11 @@ constexpr int kDim = 9;
 constexpr int kWave = 64;
 
 // ---- assignment kernel geometry -----------------------------------------------------
-// A wave scores kAssignTilesPerWave tiles of 32 kernels (a "unit" of 64 kernels, one per
-// lane) against 32-entry codebook tiles with v_mfma_f32_32x32x16_bf16 (an exact bf16 split
-// of the K = 10 fp32 contraction, 9 dims + norm, into three cross terms).  The grid is
-// persistent: one workgroup of kAssignWaves waves per CU (three per SIMD), each walking a
-// contiguous run of the stack's units, one unit per wave at a time.
+// A wave scores two tiles of 32 kernels (a "unit" of 64 kernels, one per lane) against 32-entry
+// codebook tiles on the matrix cores.  The grid is persistent: one workgroup of kAssignWaves
+// waves per CU (three per SIMD), each working through a run of one layer's units, one unit per
+// wave at a time.
 constexpr int kAssignWaves = 12;
-constexpr int kAssignTilesPerWave = 2;
-// codebook entries staged in LDS at a time by the plain assignment (64 B of operands + 48 B
-// of fp32 row each: 112 KB of the CU's 160 KB; codebooks up to this size stay resident, and
-// a larger one takes fewer chunks, each costing a staging pass between two barriers)
-constexpr int kAssignChunk = 1024;
 constexpr int kAssignGridMax = 256;  // the persistent grid: one workgroup per CU
 
 // ---- update kernel geometry ---------------------------------------------------------
@@ -117,7 +111,6 @@ __device__ __forceinline__ unsigned long long fixed_bits(float x, double scale) 
 // only its finishing launch.  A layer's partials are those of its workgroups (the grid is
 // split per layer; fused_parts(n) at most).
 constexpr int kFuseMaxK = 256;
-constexpr int kFuseChunk = 256;  // codebook entries staged at a time by the fused variant
 
 // ---- per-layer workspace ---------------------------------------------------------------
 //   assign distortion partials : fp64 [assign_units(n)]                          (overwritten each call)
@@ -287,6 +280,7 @@ constexpr int kSumThreads = 640;
 int assign_partition(const int* units, const int* ks, int nlayers, int* g);
 hipError_t launch_assign(const StackParams& p, hipStream_t s, bool fused = false, hipEvent_t start = nullptr,
                          hipEvent_t stop = nullptr);
+hipError_t launch_assign_large(const StackParams& p, hipStream_t s, hipEvent_t start, hipEvent_t stop);
 hipError_t launch_assign_finish(const StackParams& p, hipStream_t s);
 hipError_t launch_update(const StackParams& p, hipStream_t s);
 hipError_t launch_update_finish(const StackParams& p, hipStream_t s);

@@ -53,3 +53,69 @@ def test_stack_of_mixed_codebooks(shape):
         J = float(a["d32"].astype(np.float64).sum())
         assert abs(float(host(st.distortion[i])[0]) - J) <= 1e-9 * J, shape[i]
         assert abs(float(host(st.distortion[i])[1]) - J) <= 1e-9 * J, shape[i]
+
+
+# sizes at the edges of the kernels' variants: 1024 | 1025 entries (three bf16 terms | one fp16
+# term), 1920 | 1921 (fp32 rows in LDS | in memory), 2048 | 2049 (segments of 256 | 512 entries),
+# 4864 | 4865 (resident | streamed), a last segment of one tile or one entry, and kernel counts
+# with several waves per unit, one wave per unit, and more units than a streaming wave keeps
+EDGES = [(1000, 1024), (1000, 1025), (64 * 300, 1025), (1000, 1920), (1000, 1921), (700, 2048), (700, 2049),
+         (64 * 300 + 1, 2049), (500, 2561), (500, 4864), (500, 4865), (64 * 260, 4865), (300, 9217)]
+
+
+def laplace(n, seed):
+    return np.random.default_rng(seed).laplace(0.0, 0.05, (n, 9)).astype(np.float32)
+
+
+def check_assign(X, C, tag):
+    a = oracle.assign(X, C)
+    idx, bd, J = kq.kq_assign(dev(X), dev(C))
+    bad = np.nonzero(host(idx) != a["idx"])[0]
+    assert bad.size == 0, (tag, bad.size, bad[:4], host(idx)[bad[:4]], a["idx"][bad[:4]])
+    assert np.array_equal(host(bd).view(np.uint32), a["d32"].view(np.uint32)), tag
+    Jr = float(a["d32"].astype(np.float64).sum())
+    assert not np.isfinite(Jr) or abs(float(host(J)[0]) - Jr) <= 1e-9 * abs(Jr), tag
+
+
+@pytest.mark.parametrize("n,k", EDGES)
+def test_assign_at_the_edges_of_the_variants(n, k):
+    X = laplace(n, n + k)
+    check_assign(X, synth.random_codebook_state(X, k, k), (n, k))
+
+
+@pytest.mark.parametrize("k", [1500, 3000, 5000])
+def test_assign_near_ties_and_scales(k):
+    """What the fp16 screening cannot tell apart: copied entries, entries one unit in the last
+    place from each other, a codebook whose entries span many magnitudes, kernels far larger and
+    far smaller than the codebook, exact hits."""
+    rng = np.random.default_rng(k)
+    X = laplace(1200, k)
+    C = X[rng.integers(0, 1200, k)].copy()                      # copies and exact hits
+    C[::3] = np.nextafter(C[::3], np.float32(np.inf))
+    check_assign(X, C, "copies")
+    C = synth.random_codebook_state(X, k, k) * (10.0 ** rng.uniform(-12, 6, (k, 1))).astype(np.float32)
+    check_assign(X, C, "spread codebook")
+    Y = X * (10.0 ** rng.uniform(-20, 12, (1200, 1))).astype(np.float32)
+    check_assign(Y, synth.random_codebook_state(X, k, k), "spread kernels")
+    for s in (1e-30, 1e-18, 1e9, 1e17):
+        check_assign(X * np.float32(s), synth.random_codebook_state(X, k, k) * np.float32(s), f"scale {s}")
+
+
+@pytest.mark.parametrize("k", [1500, 5000])
+def test_assign_extreme_values(k):
+    rng = np.random.default_rng(k)
+    X = laplace(300, k)
+    C = synth.random_codebook_state(X, k, k)
+    for name, v in [("huge entry", 3e38), ("infinite entry", np.inf), ("zero codebook", None)]:
+        D = C.copy()
+        if v is None:
+            D[:] = 0
+        else:
+            D[rng.integers(0, k, 5)] = v
+        check_assign(X, D, name)
+    Z = X.copy()
+    Z[::7] = 0
+    Z[3] = 1e-45
+    check_assign(Z, C, "zero kernels")
+    Z[5] = 3e38
+    check_assign(Z, C, "huge kernel")
