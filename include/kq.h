@@ -387,12 +387,13 @@ kq_status kq_quantize_codebook_stack(const kq_cbq_layer* layers, int32_t n_layer
  *   codebooks spread over the whole GPU.  In KQ_CBQ_WKMEANS mode every codebook of at least
  *   16384 scalars (k >= 1821) runs the kq_quantize_scalars machinery with the entry counts
  *   as integer weights (each of an entry's 9 scalars weighs its count; weights <= 0 add
- *   nothing), one such codebook after another; the smaller ones (and every codebook of a
- *   KQ_CBQ_UNIFORM call) take one workgroup each as in kq_quantize_codebook_stack.
+ *   nothing), up to 16 such codebooks in one sequence of launches; the smaller ones (and every
+ *   codebook of a KQ_CBQ_UNIFORM call) take one workgroup each as in kq_quantize_codebook_stack.
  *   ws/ws_bytes: device workspace of at least
  *   kq_quantize_codebook_stack_workspace_bytes(layers, n_layers, bits) bytes (256-byte
  *   aligned; contents need no initialisation; NULL allowed when that size is 0 or the mode
- *   is KQ_CBQ_UNIFORM), else KQ_ERR_WORKSPACE.  Other errors as kq_quantize_codebook.
+ *   is KQ_CBQ_UNIFORM); with less, but room for the largest wide codebook alone (the size
+ *   queried for it), they run one after another; else KQ_ERR_WORKSPACE.  Other errors as kq_quantize_codebook.
  */
 size_t kq_quantize_codebook_stack_workspace_bytes(const kq_cbq_layer* layers, int32_t n_layers, int32_t bits);
 kq_status kq_quantize_codebook_stack_ws(const kq_cbq_layer* layers, int32_t n_layers, int32_t bits,

@@ -574,7 +574,7 @@ kq_status kq_quantize_scalars(const float* v, int64_t count, int32_t bits, int32
     FcParams p;
     fc_params(p, v, nullptr, count, bits, iters, codes, levels, v_hat, rounds,
               (flags & KQ_F_EXACT_SEARCH) ? 1 : ((flags & KQ_F_THRESHOLDS) ? 2 : 0), ws);
-    return hip_status(launch_fc_quantize(p, (hipStream_t)stream));
+    return hip_status(launch_fc_quantize(&p, 1, (hipStream_t)stream));
 }
 
 // a fit workspace large enough for every codebook size up to kmax (the per-layer layout
@@ -878,17 +878,32 @@ kq_status kq_quantize_codebook_stack(const kq_cbq_layer* layers, int32_t n_layer
 // on the whole GPU: below, its per-round launches cost more than one workgroup's pass
 constexpr int64_t kCbqWideMin = 16384;
 
+static bool cbq_wide(const kq_cbq_layer& l) {
+    return l.k >= 1 && l.k <= KQ_MAX_K && (int64_t)l.k * KQ_DIM >= kCbqWideMin;
+}
+
+// the largest workspace of one wide codebook
+static size_t cbq_wide_one(const kq_cbq_layer* layers, int32_t n_layers, int32_t bits) {
+    size_t b = 0;
+    for (int32_t l = 0; l < n_layers; ++l)
+        if (cbq_wide(layers[l])) b = std::max(b, fc_ws_bytes((int64_t)layers[l].k * KQ_DIM, bits));
+    return b;
+}
+
+// The wide codebooks share their launches, up to KQ_MAX_STACK at a time, each in a region of its
+// own; a workspace for one of them at a time (the largest) is accepted too: they then run one
+// after another.
 size_t kq_quantize_codebook_stack_workspace_bytes(const kq_cbq_layer* layers, int32_t n_layers, int32_t bits) {
     if (layers == nullptr || n_layers < 1 || bits < 1 || bits > 8) return 0;
-    size_t b = 0;
+    size_t most = 0, sum = 0;
+    int n = 0;
     for (int32_t l = 0; l < n_layers; ++l) {
-        const int64_t m = (int64_t)layers[l].k * KQ_DIM;
-        if (layers[l].k >= 1 && layers[l].k <= KQ_MAX_K && m >= kCbqWideMin) {
-            const size_t f = fc_ws_bytes(m, bits);
-            b = f > b ? f : b;
-        }
+        if (!cbq_wide(layers[l])) continue;
+        sum += fc_ws_bytes((int64_t)layers[l].k * KQ_DIM, bits);
+        most = std::max(most, sum);
+        if (++n == KQ_MAX_STACK) n = 0, sum = 0;
     }
-    return b;
+    return most;
 }
 
 kq_status kq_quantize_codebook_stack_ws(const kq_cbq_layer* layers, int32_t n_layers, int32_t bits, int32_t mode,
@@ -898,7 +913,7 @@ kq_status kq_quantize_codebook_stack_ws(const kq_cbq_layer* layers, int32_t n_la
         const kq_status st = check_cbq(layers[l], bits, mode, iters);
         if (st != KQ_OK) return st;
     }
-    const size_t need = kq_quantize_codebook_stack_workspace_bytes(layers, n_layers, bits);
+    const size_t need = cbq_wide_one(layers, n_layers, bits);
     if (need > 0 && mode == KQ_CBQ_WKMEANS) {
         const kq_status w = check_ws(ws, ws_bytes, need);
         if (w != KQ_OK) return w;
@@ -920,16 +935,27 @@ kq_status kq_quantize_codebook_stack_ws(const kq_cbq_layer* layers, int32_t n_la
         const kq_status st = kq_quantize_codebook_stack(small, ns, bits, mode, iters, stream);
         if (st != KQ_OK) return st;
     }
-    // the large ones one after another on the whole GPU, reusing the workspace (stream order)
+    // the large ones on the whole GPU, as many per sequence of launches as the workspace holds
+    // (the next sequence reuses it: stream order)
     if (mode != KQ_CBQ_WKMEANS) return KQ_OK;
+    FcParams set[KQ_MAX_STACK];
+    int n = 0;
+    size_t off = 0;
     for (int32_t l = 0; l < n_layers; ++l) {
         const kq_cbq_layer& s = layers[l];
         const int64_t m = (int64_t)s.k * KQ_DIM;
         if (m < kCbqWideMin) continue;
-        FcParams p;
-        fc_params(p, s.C, s.weights, m, bits, iters, s.codes, s.levels, s.C_hat, nullptr, 0, ws);
-        if (launch_fc_quantize(p, (hipStream_t)stream) != hipSuccess) return KQ_ERR_HIP;
+        const size_t b = fc_ws_bytes(m, bits);
+        if (n == KQ_MAX_STACK || off + b > ws_bytes) {
+            if (launch_fc_quantize(set, n, (hipStream_t)stream) != hipSuccess) return KQ_ERR_HIP;
+            n = 0;
+            off = 0;
+        }
+        fc_params(set[n++], s.C, s.weights, m, bits, iters, s.codes, s.levels, s.C_hat, nullptr, 1,
+                  (unsigned char*)ws + off);
+        off += b;
     }
+    if (n > 0 && launch_fc_quantize(set, n, (hipStream_t)stream) != hipSuccess) return KQ_ERR_HIP;
     return KQ_OK;
 }
 
@@ -1137,7 +1163,9 @@ struct CompressLayout {
     size_t fit, cbq, recon, total;
 };
 
-static CompressLayout compress_layout(const kq_compress_layer* layers, int32_t n_layers, int32_t bits) {
+// one_cbq: room for one wide codebook at a time only
+static CompressLayout compress_layout(const kq_compress_layer* layers, int32_t n_layers, int32_t bits,
+                                      bool one_cbq = false) {
     CompressLayout L = {0, 0, 0, 0};
     for (int32_t l0 = 0; l0 < n_layers; l0 += KQ_MAX_STACK) {
         const int32_t l1 = (n_layers - l0 < KQ_MAX_STACK) ? n_layers : l0 + KQ_MAX_STACK;
@@ -1153,7 +1181,8 @@ static CompressLayout compress_layout(const kq_compress_layer* layers, int32_t n
             if (layers[l].W_hat) rec[nrec++] = r;
         }
         const size_t f = stack_ws_bytes(fit, l1 - l0);
-        const size_t c = kq_quantize_codebook_stack_workspace_bytes(cbq, l1 - l0, bits);
+        const size_t c = one_cbq ? cbq_wide_one(cbq, l1 - l0, bits)
+                                 : kq_quantize_codebook_stack_workspace_bytes(cbq, l1 - l0, bits);
         const size_t r = nrec ? recon_ws_bytes(rec, nrec) : 0;
         L.fit = f > L.fit ? f : L.fit;
         L.cbq = align256(c) > L.cbq ? align256(c) : L.cbq;
@@ -1173,7 +1202,8 @@ kq_status kq_compress_stack(const kq_compress_layer* layers, int32_t n_layers, i
                             size_t ws_bytes, void* stream) {
     kq_status st = check_compress(layers, n_layers, iters, mode, bits, cbq_iters, flags);
     if (st != KQ_OK) return st;
-    const CompressLayout L = compress_layout(layers, n_layers, bits);
+    CompressLayout L = compress_layout(layers, n_layers, bits);
+    if (ws_bytes < L.total) L = compress_layout(layers, n_layers, bits, true);  // still enough
     if ((st = check_ws(ws, ws_bytes, L.total)) != KQ_OK) return st;
     hipStream_t s = (hipStream_t)stream;
     unsigned char* w = (unsigned char*)ws;

@@ -12,6 +12,8 @@
 // a pure function of the codebook and the weights.
 #include <type_traits>
 
+#include <string.h>
+
 #include "kq_internal.h"
 
 namespace kq {
@@ -750,6 +752,9 @@ __global__ __launch_bounds__(kCbqThreads) void cbq_kernel(const CbqParams p) {
 //                     levels while fewer than `iters` updates were made.
 // Integer sums make the levels, and with them the codes, independent of the grid and the
 // order of the work: the result is the single-workgroup quantizer's, bit for bit.
+// A launch serves up to KQ_MAX_STACK sets (blockIdx.y): one large one, or the large codebooks of
+// a stack, whose rounds would each leave the chip idle (ten codebooks of 20,727 to 69,111 scalars
+// one after another: 3 launches of 3 to 7 us for each round of each, 5.3 ms; together 0.6 ms).
 constexpr int kFcCols = kDigits + 1;  // digits, then the count
 // scalars from which codes come from thresholds: below, the per-round boundary search costs
 // more than the exact search it saves (measured per round: about even at 2^21 scalars,
@@ -764,8 +769,22 @@ __host__ __device__ __forceinline__ bool fc_thr_wanted(const FcParams& p) {
 
 __device__ __forceinline__ bool fc_done(const FcParams& p) { return p.state[0] != 0; }
 
+// the launch's sets; a set uses the first G workgroups of its row of the grid.  (A single set
+// has an argument block of its own: 3 KB of arguments cost each launch 0.3 us more.)
+template <int NS>
+struct FcStack {
+    FcParams L[NS];
+};
+template <int NS>
+__device__ __forceinline__ const FcParams& fc_set(const FcStack<NS>& st) {
+    return st.L[NS == 1 ? 0 : blockIdx.y];
+}
+
 // per workgroup: min and max of its scalars
-__global__ __launch_bounds__(kFcThreads) void fc_minmax_kernel(const FcParams p) {
+template <int NS>
+__global__ __launch_bounds__(kFcThreads) void fc_minmax_kernel(const FcStack<NS> st) {
+    const FcParams& p = fc_set(st);
+    if ((int)blockIdx.x >= p.G) return;
     __shared__ float s_lo[kFcThreads / kWave], s_hi[kFcThreads / kWave];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     float lo = __builtin_inff(), hi = -__builtin_inff();
@@ -779,7 +798,7 @@ __global__ __launch_bounds__(kFcThreads) void fc_minmax_kernel(const FcParams p)
         const long long ng = p.m >> 2;
         const float4* __restrict__ v4 = reinterpret_cast<const float4*>(p.v);
         for (long long g0 = (long long)blockIdx.x * kFcThreads * kPer + tid; g0 < ng;
-             g0 += (long long)gridDim.x * kFcThreads * kPer) {
+             g0 += (long long)p.G * kFcThreads * kPer) {
             float4 xv[kPer];
 #pragma unroll
             for (int j = 0; j < kPer; ++j) {
@@ -797,7 +816,7 @@ __global__ __launch_bounds__(kFcThreads) void fc_minmax_kernel(const FcParams p)
         }
         r0 = 4 * ng;
     }
-    for (long long r = r0 + (long long)blockIdx.x * kFcThreads + tid; r < p.m; r += (long long)gridDim.x * kFcThreads)
+    for (long long r = r0 + (long long)blockIdx.x * kFcThreads + tid; r < p.m; r += (long long)p.G * kFcThreads)
         take(p.v[r]);
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
@@ -896,7 +915,10 @@ __device__ void set_thresholds(const FcParams& p, const float* s_lev, int nlev, 
 }
 
 // the uniform grid on [min, max]; clears the run state and the running sums
-__global__ __launch_bounds__(kCbqMaxLevels) void fc_grid_kernel(const FcParams p, int nblk) {
+template <int NS>
+__global__ __launch_bounds__(kCbqMaxLevels) void fc_grid_kernel(const FcStack<NS> st) {
+    const FcParams& p = fc_set(st);
+    const int nblk = p.G;
     __shared__ float s_lo, s_hi;
     __shared__ float s_lev[kCbqMaxLevels];
     __shared__ int s_unsorted, s_bad;
@@ -953,8 +975,10 @@ __global__ __launch_bounds__(kCbqMaxLevels) void fc_grid_kernel(const FcParams p
 // THR: the launch for rounds whose codes come from thresholds (true) or from the exact
 // searches (false); the state decides on the device, and the other launch returns at once.
 // Apart, the light threshold code keeps its register count low.
-template <bool INIT, int NLEV, bool THR>
-__global__ __launch_bounds__(kFcThreads) void fc_assign_kernel(const FcParams p) {
+template <int NS, bool INIT, int NLEV, bool THR>
+__global__ __launch_bounds__(kFcThreads) void fc_assign_kernel(const FcStack<NS> st) {
+    const FcParams& p = fc_set(st);
+    if ((int)blockIdx.x >= p.G) return;
     __shared__ __attribute__((aligned(16))) float s_lev[NLEV < 8 ? 8 : NLEV];
     __shared__ __attribute__((aligned(16))) float s_thr[NLEV < 8 ? 8 : NLEV];
     __shared__ unsigned long long s_dig[NLEV * kFcCols];
@@ -1087,7 +1111,7 @@ __global__ __launch_bounds__(kFcThreads) void fc_assign_kernel(const FcParams p)
             // coded; a group whose codes change stores its word
             constexpr int kGPer = 2;
             const long long ng = m >> 2;
-            const long long step = (long long)gridDim.x * kFcThreads * kGPer;
+            const long long step = (long long)p.G * kFcThreads * kGPer;
             const float4* __restrict__ v4 = reinterpret_cast<const float4*>(p.v);
             unsigned* __restrict__ c4 = reinterpret_cast<unsigned*>(p.codes);
             auto load = [&](long long g0, float4 (&xv)[kGPer], unsigned (&cw)[kGPer]) {
@@ -1177,7 +1201,7 @@ __global__ __launch_bounds__(kFcThreads) void fc_assign_kernel(const FcParams p)
                     if (INIT || q != (int)p.codes[r]) p.codes[r] = (uint8_t)q;
                 }
         } else {
-            const long long step = (long long)gridDim.x * kFcThreads * kPer;
+            const long long step = (long long)p.G * kFcThreads * kPer;
             for (long long r0 = (long long)blockIdx.x * kFcThreads * kPer + tid; r0 < m; r0 += step) {
                 float x[kPer];
                 int c[kPer];
@@ -1221,20 +1245,23 @@ __global__ __launch_bounds__(kFcThreads) void fc_assign_kernel(const FcParams p)
     unsigned long long* part = (unsigned long long*)p.part;
     for (int e = tid; e < NLEV * kFcCols; e += kFcThreads) {
         const int q = e / kFcCols, c = e - q * kFcCols;
-        part[((size_t)q * gridDim.x + blockIdx.x) * kFcCols + c] = s_dig[e];
+        part[((size_t)q * p.G + blockIdx.x) * kFcCols + c] = s_dig[e];
     }
     if (tid == 0) p.wg_changed[blockIdx.x] = INIT ? 1 : s_changed;
 }
 
-template <bool INIT>
-hipError_t launch_fc_assign(const FcParams& p, int G, hipStream_t s) {
-    // the threshold launch only where the state may choose thresholds
-    const bool thr = fc_thr_wanted(p);
-    switch (p.bits) {
-#define KQ_FC_CASE(B)                                                                                          \
-    case B:                                                                                                    \
-        if (thr) hipLaunchKernelGGL((fc_assign_kernel<INIT, (1 << B), true>), dim3(G), dim3(kFcThreads), 0, s, p); \
-        hipLaunchKernelGGL((fc_assign_kernel<INIT, (1 << B), false>), dim3(G), dim3(kFcThreads), 0, s, p);       \
+template <int NS, bool INIT>
+hipError_t launch_fc_assign(const FcStack<NS>& st, dim3 G, hipStream_t s) {
+    // the threshold launch only where the state may choose thresholds (the sets of a launch are
+    // one unweighted set, or codebooks, which never do)
+    const bool thr = NS == 1 && fc_thr_wanted(st.L[0]);
+    switch (st.L[0].bits) {
+#define KQ_FC_CASE(B)                                                                                                \
+    case B:                                                                                                          \
+        if constexpr (NS == 1) {                                                                                     \
+            if (thr) hipLaunchKernelGGL((fc_assign_kernel<1, INIT, (1 << B), true>), G, dim3(kFcThreads), 0, s, st); \
+        }                                                                                                            \
+        hipLaunchKernelGGL((fc_assign_kernel<NS, INIT, (1 << B), false>), G, dim3(kFcThreads), 0, s, st);            \
         break;
         KQ_FC_CASE(1)
         KQ_FC_CASE(2)
@@ -1285,7 +1312,10 @@ __device__ __forceinline__ long long wave_sum_i64(long long v) {
 // contiguous); a workgroup whose codes did not change added nothing and is skipped (every
 // first-pass partial is read)
 constexpr int kFcSumThreads = kFcGrid;
-__global__ __launch_bounds__(kFcSumThreads) void fc_sum_kernel(const FcParams p, int nblk) {
+template <int NS>
+__global__ __launch_bounds__(kFcSumThreads) void fc_sum_kernel(const FcStack<NS> st) {
+    const FcParams& p = fc_set(st);
+    const int nblk = p.G;
     __shared__ long long s_acc[kFcSumThreads / kWave][kFcCols];
     if (fc_done(p)) return;
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1322,7 +1352,10 @@ __global__ __launch_bounds__(kFcSumThreads) void fc_sum_kernel(const FcParams p,
 }
 
 // run state: stop after a round without a changed code, else take the candidates
-__global__ __launch_bounds__(kCbqMaxLevels) void fc_state_kernel(const FcParams p, int nblk) {
+template <int NS>
+__global__ __launch_bounds__(kCbqMaxLevels) void fc_state_kernel(const FcStack<NS> st) {
+    const FcParams& p = fc_set(st);
+    const int nblk = p.G;
     __shared__ int s_any, s_unsorted, s_bad;
     __shared__ float s_lev[kCbqMaxLevels];
     if (fc_done(p)) return;
@@ -1354,7 +1387,10 @@ __global__ __launch_bounds__(kCbqMaxLevels) void fc_state_kernel(const FcParams 
     }
 }
 
-__global__ __launch_bounds__(kFcThreads) void fc_output_kernel(const FcParams p) {
+template <int NS>
+__global__ __launch_bounds__(kFcThreads) void fc_output_kernel(const FcStack<NS> st) {
+    const FcParams& p = fc_set(st);
+    if ((int)blockIdx.x >= p.G) return;
     __shared__ float s_lev[kCbqMaxLevels];
     const int tid = threadIdx.x, nlev = 1 << p.bits;
     for (int e = tid; e < nlev; e += kFcThreads) s_lev[e] = p.lev[e];
@@ -1372,7 +1408,7 @@ __global__ __launch_bounds__(kFcThreads) void fc_output_kernel(const FcParams p)
         const unsigned* __restrict__ c4 = reinterpret_cast<const unsigned*>(p.codes);
         float4* __restrict__ o4 = reinterpret_cast<float4*>(p.v_hat);
         for (long long g0 = (long long)blockIdx.x * kFcThreads * kPer + tid; g0 < ng;
-             g0 += (long long)gridDim.x * kFcThreads * kPer) {
+             g0 += (long long)p.G * kFcThreads * kPer) {
             unsigned cw[kPer];
 #pragma unroll
             for (int j = 0; j < kPer; ++j) {
@@ -1389,7 +1425,7 @@ __global__ __launch_bounds__(kFcThreads) void fc_output_kernel(const FcParams p)
         }
         r0 = 4 * ng;
     }
-    for (long long r = r0 + (long long)blockIdx.x * kFcThreads + tid; r < p.m; r += (long long)gridDim.x * kFcThreads)
+    for (long long r = r0 + (long long)blockIdx.x * kFcThreads + tid; r < p.m; r += (long long)p.G * kFcThreads)
         p.v_hat[r] = s_lev[p.codes[r]];
 }
 
@@ -1398,25 +1434,39 @@ int fc_grid(long long m) {
     return (int)(b < kFcGrid ? (b < 1 ? 1 : b) : kFcGrid);
 }
 
-hipError_t launch_fc_quantize(const FcParams& p, hipStream_t s) {
-    const int G = fc_grid(p.m), nlev = 1 << p.bits;
-    hipLaunchKernelGGL(fc_minmax_kernel, dim3(G), dim3(kFcThreads), 0, s, p);
+template <int NS>
+hipError_t launch_fc_sets(const FcParams* sets, int n, hipStream_t s) {
+    FcStack<NS> st;
+    memset(&st, 0, sizeof(st));
+    int gmax = 1;
+    for (int l = 0; l < n; ++l) {
+        st.L[l] = sets[l];
+        st.L[l].G = fc_grid(sets[l].m);
+        gmax = st.L[l].G > gmax ? st.L[l].G : gmax;
+    }
+    const int nlev = 1 << sets[0].bits, iters = sets[0].iters;
+    const dim3 G(gmax, n), one(1, n);
+    hipLaunchKernelGGL(fc_minmax_kernel<NS>, G, dim3(kFcThreads), 0, s, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fc_grid_kernel, dim3(1), dim3(kCbqMaxLevels), 0, s, p, G);
+    hipLaunchKernelGGL(fc_grid_kernel<NS>, one, dim3(kCbqMaxLevels), 0, s, st);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // the initial codes and sums, then `iters` rounds of (levels, codes)
-    for (int r = 0; r <= p.iters; ++r) {
-        e = r == 0 ? launch_fc_assign<true>(p, G, s) : launch_fc_assign<false>(p, G, s);
+    for (int r = 0; r <= iters; ++r) {
+        e = r == 0 ? launch_fc_assign<NS, true>(st, G, s) : launch_fc_assign<NS, false>(st, G, s);
         if (e != hipSuccess) return e;
-        if (r == p.iters) break;  // the last codes need no further levels
-        hipLaunchKernelGGL(fc_sum_kernel, dim3(nlev), dim3(kFcSumThreads), 0, s, p, G);
+        if (r == iters) break;  // the last codes need no further levels
+        hipLaunchKernelGGL(fc_sum_kernel<NS>, dim3(nlev, n), dim3(kFcSumThreads), 0, s, st);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(fc_state_kernel, dim3(1), dim3(kCbqMaxLevels), 0, s, p, G);
+        hipLaunchKernelGGL(fc_state_kernel<NS>, one, dim3(kCbqMaxLevels), 0, s, st);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(fc_output_kernel, dim3(G), dim3(kFcThreads), 0, s, p);
+    hipLaunchKernelGGL(fc_output_kernel<NS>, G, dim3(kFcThreads), 0, s, st);
     return hipGetLastError();
+}
+
+hipError_t launch_fc_quantize(const FcParams* sets, int n, hipStream_t s) {
+    return n == 1 ? launch_fc_sets<1>(sets, 1, s) : launch_fc_sets<KQ_MAX_STACK>(sets, n, s);
 }
 
 hipError_t launch_cbq(const CbqParams& p, hipStream_t s) {

@@ -329,6 +329,7 @@ struct FcParams {
     int* state;            // [0] converged, [1] level updates made, [2] levels unsorted, [3] thresholds valid
     int* wg_changed;       // [grid] a code changed in the workgroup
     unsigned* tbl;         // [kFcBuckets][2] bucket table of the thresholds (range[3] > 0: valid)
+    int G;                 // workgroups of this set (fc_grid(m); filled by the launcher)
 };
 // threshold rounds: the data range is cut into this many buckets of equal width; a scalar's
 // bucket gives the count of the thresholds below the bucket and the first one inside it
@@ -340,7 +341,9 @@ inline size_t fc_ws_bytes(long long m, int bits) {
            align256(sizeof(long long) * nlev * 12) + 3 * align256(sizeof(float) * nlev) + align256(sizeof(int) * 4) +
            align256(sizeof(int) * G) + align256(sizeof(unsigned) * 2 * kFcBuckets);
 }
-hipError_t launch_fc_quantize(const FcParams& p, hipStream_t s);
+// n sets (at most KQ_MAX_STACK) in one sequence of launches: one unweighted set, or weighted
+// codebooks; all of the same bits, iters and thr_mode
+hipError_t launch_fc_quantize(const FcParams* sets, int n, hipStream_t s);
 
 // stack forms of pack and reconstruct (+ squared error): a compact unit table first
 struct PackJob {

@@ -119,3 +119,23 @@ def test_assign_extreme_values(k):
     check_assign(Z, C, "zero kernels")
     Z[5] = 3e38
     check_assign(Z, C, "huge kernel")
+
+
+@pytest.mark.parametrize("bits", [2, 6])
+def test_wide_codebooks_share_their_launches(bits):
+    """Codebooks of at least 16384 scalars of several sizes, some weights zero: together (the
+    queried workspace), one after another (a workspace for the largest alone) and in one workgroup
+    each give the same codes and levels; more of them than one sequence of launches takes."""
+    rng = np.random.default_rng(bits)
+    ks = [1821, 3000, 1900, 100, 4096] + [1830 + i for i in range(14)]
+    Cs = [dev(rng.laplace(0, 0.03, (k, 9)).astype(np.float32)) for k in ks]
+    ws = [dev(rng.integers(0, 50, k).astype(np.int32)) for k in ks]
+    one = kq.kq_quantize_codebook_stack(Cs, ws, bits, wide=False)
+    together = kq.kq_quantize_codebook_stack(Cs, ws, bits)
+    arr = (kq.KqCbqLayer * 1)(kq.KqCbqLayer(Cs[4].data_ptr(), 4096, None, None, None, None))
+    least = kq.lib.kq_quantize_codebook_stack_workspace_bytes(arr, 1, bits)
+    alone = kq.kq_quantize_codebook_stack(Cs, ws, bits, workspace=torch.empty(least, dtype=torch.uint8, device=DEV))
+    for a, b, c in zip(one, together, alone):
+        for x, y, z in zip(a, b, c):
+            assert torch.equal(x.view(torch.uint8), y.view(torch.uint8))
+            assert torch.equal(x.view(torch.uint8), z.view(torch.uint8))
