@@ -25,9 +25,14 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libkq.so")
 
-if not os.path.exists(LIB_PATH):
-    raise ImportError(f"{LIB_PATH} is not built; run __graft_entry__.build() "
-                      "(or python paper_2003_05148_amd/_build.py)")
+HOST_PATH = os.path.join(_HERE, "_kqhost.so")
+
+for _p in (LIB_PATH, HOST_PATH):
+    if not os.path.exists(_p):
+        raise ImportError(f"{_p} is not built; run __graft_entry__.build() "
+                          "(or python paper_2003_05148_amd/_build.py)")
+
+from . import _kqhost  # noqa: E402  (after torch: it links against its libraries)
 
 _P = ctypes.c_void_p
 _I32, _I64, _U32, _SZ = ctypes.c_int32, ctypes.c_int64, ctypes.c_uint32, ctypes.c_size_t
@@ -152,7 +157,10 @@ def _check(status: int, where: str):
 
 
 def _stream(device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    i = device.index
+    if i is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(i)  # the same handle, without a Stream object around it
 
 
 def _dev(t: torch.Tensor, dtype, name: str, shape=None):
@@ -162,7 +170,7 @@ def _dev(t: torch.Tensor, dtype, name: str, shape=None):
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
     return t
 
@@ -172,12 +180,14 @@ def _ptr(t):
 
 
 def _kernels(X: torch.Tensor, name="X"):
-    if X.dim() == 4:  # an OIHW 3x3 conv weight: kernel i = o * C_in + c
+    d = X.dim()
+    if d == 4:  # an OIHW 3x3 conv weight: kernel i = o * C_in + c
         if X.shape[2] * X.shape[3] != KQ_DIM:
             raise ValueError("only 3x3 kernels are supported")
         X = X.reshape(-1, KQ_DIM)
+        d = 2
     _dev(X, torch.float32, name)
-    if X.dim() != 2 or X.shape[1] != KQ_DIM:
+    if d != 2 or X.shape[1] != KQ_DIM:
         raise ValueError(f"{name} must be [n, 9] (or an OIHW 3x3 weight)")
     return X
 
@@ -200,7 +210,7 @@ _workspaces: dict = {}
 
 
 def _ws(device, nbytes):
-    key = torch.device(device).index if torch.device(device).index is not None else torch.cuda.current_device()
+    key = device.index if device.index is not None else torch.cuda.current_device()
     w = _workspaces.get(key)
     if w is None:
         w = _workspaces[key] = Workspace(torch.device("cuda", key))
@@ -216,12 +226,18 @@ def kq_assign(X, C, idx=None, best_d=None, distortion=None, workspace=None):
     C = _kernels(C, "C")
     n, k = X.shape[0], C.shape[0]
     dev = X.device
-    idx = idx if idx is not None else torch.empty(n, dtype=torch.int32, device=dev)
-    best_d = best_d if best_d is not None else torch.empty(n, dtype=torch.float32, device=dev)
-    distortion = distortion if distortion is not None else torch.empty(1, dtype=torch.float64, device=dev)
-    _dev(idx, torch.int32, "idx", (n,))
-    _dev(best_d, torch.float32, "best_d", (n,))
-    _dev(distortion, torch.float64, "distortion")
+    if idx is None:
+        idx = torch.empty(n, dtype=torch.int32, device=dev)
+    else:
+        _dev(idx, torch.int32, "idx", (n,))
+    if best_d is None:
+        best_d = torch.empty(n, dtype=torch.float32, device=dev)
+    else:
+        _dev(best_d, torch.float32, "best_d", (n,))
+    if distortion is None:
+        distortion = torch.empty(1, dtype=torch.float64, device=dev)
+    else:
+        _dev(distortion, torch.float64, "distortion")
     nb = lib.kq_workspace_bytes(KQ_OP_ASSIGN, n, k, KQ_DIM)
     ws = workspace if workspace is not None else _ws(dev, nb)
     _check(lib.kq_assign(X.data_ptr(), n, KQ_DIM, C.data_ptr(), k, idx.data_ptr(), best_d.data_ptr(),
@@ -748,6 +764,12 @@ def kq_reconstruct_stack(layers, workspace=None):
     needs W_ref).  Returns the list of W_hat tensors."""
     if not 1 <= len(layers) <= KQ_MAX_STACK:
         raise ValueError(f"1..{KQ_MAX_STACK} layers per call")
+    plain = _kqhost.recon_args(layers)
+    if plain is not None and not plain[3]:  # no squared errors: no workspace
+        arr, outs, i, _ = plain
+        _check(lib.kq_reconstruct_stack(arr, len(layers), _ptr(workspace), 0 if workspace is None else workspace.numel(),
+                                        torch._C._cuda_getCurrentRawStream(i)), "kq_reconstruct_stack")
+        return outs
     arr, outs, dev = _recon_array(layers)
     nb = lib.kq_reconstruct_stack_workspace_bytes(ctypes.cast(arr, _P), len(layers))
     ws = workspace if workspace is not None else (_ws(dev, nb) if nb else None)

@@ -1,4 +1,5 @@
-"""Build libkq.so (HIP, gfx950) in-tree.  Used by __graft_entry__.build()."""
+"""Build libkq.so (HIP, gfx950) and _kqhost.so (the binding's host helper) in-tree.  Used by
+__graft_entry__.build()."""
 from __future__ import annotations
 
 import glob
@@ -8,6 +9,7 @@ import subprocess
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libkq.so")
+HOST_LIB = os.path.join(PKG, "_kqhost.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -40,5 +42,27 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+def build_host(verbose: bool = False) -> str:
+    """The host helper: no GPU code, compiled against the installed torch."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    tmp = HOST_LIB + f".tmp{os.getpid()}"
+    inc = [os.path.join(ROOT, "include"), sysconfig.get_paths()["include"], *cpp_extension.include_paths()]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *[f"-I{d}" for d in inc],
+           os.path.join(PKG, "csrc", "kq_host.cpp"), f"-L{lib}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", tmp]
+    if verbose:
+        print(" ".join(cmd))
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed ({r.returncode}):\n{r.stdout}{r.stderr}")
+    os.replace(tmp, HOST_LIB)
+    return HOST_LIB
+
+
 if __name__ == "__main__":
     print(build(verbose=True))
+    print(build_host(verbose=True))

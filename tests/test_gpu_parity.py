@@ -566,3 +566,35 @@ def test_quantize_codebook_6bit_rounds_bit_exact_over_many_codebooks():
         assert np.array_equal(host(codes), oc), i
         assert np.array_equal(host(levels).view(np.uint32), ol.view(np.uint32)), i
         assert np.array_equal(host(C_hat).view(np.uint32), oh.view(np.uint32)), i
+
+
+def test_reconstruct_stack_argument_forms():
+    """The native argument path (plain tensors, outputs given) and the general one (outputs made,
+    4-D weights, numpy sizes) give the same tensors; what the general one refuses is refused."""
+    rng = np.random.default_rng(5)
+    k, ns = 300, [64, 1000, 77]
+    C = [dev(rng.standard_normal((k, 9)).astype(np.float32)) for _ in ns]
+    idx = [dev(rng.integers(0, k, n).astype(np.int32)) for n in ns]
+    W = [torch.empty(n, 9, device=DEV) for n in ns]
+    plain = [{"C": c, "n": n, "idx": i, "W_hat": w} for c, n, i, w in zip(C, ns, idx, W)]
+    assert kq._kqhost.recon_args(plain) is not None
+    out = kq.kq_reconstruct_stack(plain)
+    assert all(o is w for o, w in zip(out, W))
+    made = kq.kq_reconstruct_stack([{"C": c.reshape(-1, 1, 3, 3), "n": np.int64(n), "idx": i}
+                                    for c, n, i in zip(C, ns, idx)])
+    packed = [{"C": c, "n": n, "packed": kq.kq_pack_bits(i, 9), "bits": 9, "W_hat": torch.empty_like(w)}
+              for c, n, i, w in zip(C, ns, idx, W)]
+    assert kq._kqhost.recon_args(packed) is not None
+    for a, b, c, i, cb in zip(out, made, kq.kq_reconstruct_stack(packed), idx, C):
+        ref = cb[i.long()]
+        assert torch.equal(a, ref) and torch.equal(b, ref) and torch.equal(c, ref)
+    bad = [dict(plain[0], W_hat=torch.empty(65, 9, device=DEV)), dict(plain[0], idx=idx[1]),
+           dict(plain[0], C=C[0].double()), dict(plain[0], W_hat=torch.empty(9, 64, device=DEV).t()),
+           dict(plain[0], C=C[0].cpu()), dict(plain[0], sq_error=torch.zeros(1, device=DEV))]
+    for d in bad:
+        with pytest.raises((TypeError, ValueError)):
+            kq.kq_reconstruct_stack([d])
+    with pytest.raises(KeyError):
+        kq.kq_reconstruct_stack([{"n": 64}])
+    with pytest.raises(kq.KqError):
+        kq.kq_reconstruct_stack([dict(packed[0], bits=17)])
