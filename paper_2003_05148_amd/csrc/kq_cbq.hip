@@ -779,12 +779,18 @@ template <int NS>
 __device__ __forceinline__ const FcParams& fc_set(const FcStack<NS>& st) {
     return st.L[NS == 1 ? 0 : blockIdx.y];
 }
+// the set's workgroups, in a launch whose grid has them along x (a single set's are the grid)
+template <int NS>
+__device__ __forceinline__ int fc_blocks(const FcStack<NS>& st) {
+    return NS == 1 ? (int)gridDim.x : fc_set(st).G;
+}
 
 // per workgroup: min and max of its scalars
 template <int NS>
 __global__ __launch_bounds__(kFcThreads) void fc_minmax_kernel(const FcStack<NS> st) {
     const FcParams& p = fc_set(st);
-    if ((int)blockIdx.x >= p.G) return;
+    const int nblk = fc_blocks(st);
+    if (NS > 1 && (int)blockIdx.x >= nblk) return;
     __shared__ float s_lo[kFcThreads / kWave], s_hi[kFcThreads / kWave];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     float lo = __builtin_inff(), hi = -__builtin_inff();
@@ -798,7 +804,7 @@ __global__ __launch_bounds__(kFcThreads) void fc_minmax_kernel(const FcStack<NS>
         const long long ng = p.m >> 2;
         const float4* __restrict__ v4 = reinterpret_cast<const float4*>(p.v);
         for (long long g0 = (long long)blockIdx.x * kFcThreads * kPer + tid; g0 < ng;
-             g0 += (long long)p.G * kFcThreads * kPer) {
+             g0 += (long long)nblk * kFcThreads * kPer) {
             float4 xv[kPer];
 #pragma unroll
             for (int j = 0; j < kPer; ++j) {
@@ -816,7 +822,7 @@ __global__ __launch_bounds__(kFcThreads) void fc_minmax_kernel(const FcStack<NS>
         }
         r0 = 4 * ng;
     }
-    for (long long r = r0 + (long long)blockIdx.x * kFcThreads + tid; r < p.m; r += (long long)p.G * kFcThreads)
+    for (long long r = r0 + (long long)blockIdx.x * kFcThreads + tid; r < p.m; r += (long long)nblk * kFcThreads)
         take(p.v[r]);
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
@@ -978,7 +984,8 @@ __global__ __launch_bounds__(kCbqMaxLevels) void fc_grid_kernel(const FcStack<NS
 template <int NS, bool INIT, int NLEV, bool THR>
 __global__ __launch_bounds__(kFcThreads) void fc_assign_kernel(const FcStack<NS> st) {
     const FcParams& p = fc_set(st);
-    if ((int)blockIdx.x >= p.G) return;
+    const int nblk = fc_blocks(st);
+    if (NS > 1 && (int)blockIdx.x >= nblk) return;
     __shared__ __attribute__((aligned(16))) float s_lev[NLEV < 8 ? 8 : NLEV];
     __shared__ __attribute__((aligned(16))) float s_thr[NLEV < 8 ? 8 : NLEV];
     __shared__ unsigned long long s_dig[NLEV * kFcCols];
@@ -1111,7 +1118,7 @@ __global__ __launch_bounds__(kFcThreads) void fc_assign_kernel(const FcStack<NS>
             // coded; a group whose codes change stores its word
             constexpr int kGPer = 2;
             const long long ng = m >> 2;
-            const long long step = (long long)p.G * kFcThreads * kGPer;
+            const long long step = (long long)nblk * kFcThreads * kGPer;
             const float4* __restrict__ v4 = reinterpret_cast<const float4*>(p.v);
             unsigned* __restrict__ c4 = reinterpret_cast<unsigned*>(p.codes);
             auto load = [&](long long g0, float4 (&xv)[kGPer], unsigned (&cw)[kGPer]) {
@@ -1201,7 +1208,7 @@ __global__ __launch_bounds__(kFcThreads) void fc_assign_kernel(const FcStack<NS>
                     if (INIT || q != (int)p.codes[r]) p.codes[r] = (uint8_t)q;
                 }
         } else {
-            const long long step = (long long)p.G * kFcThreads * kPer;
+            const long long step = (long long)nblk * kFcThreads * kPer;
             for (long long r0 = (long long)blockIdx.x * kFcThreads * kPer + tid; r0 < m; r0 += step) {
                 float x[kPer];
                 int c[kPer];
@@ -1245,7 +1252,7 @@ __global__ __launch_bounds__(kFcThreads) void fc_assign_kernel(const FcStack<NS>
     unsigned long long* part = (unsigned long long*)p.part;
     for (int e = tid; e < NLEV * kFcCols; e += kFcThreads) {
         const int q = e / kFcCols, c = e - q * kFcCols;
-        part[((size_t)q * p.G + blockIdx.x) * kFcCols + c] = s_dig[e];
+        part[((size_t)q * nblk + blockIdx.x) * kFcCols + c] = s_dig[e];
     }
     if (tid == 0) p.wg_changed[blockIdx.x] = INIT ? 1 : s_changed;
 }
@@ -1390,7 +1397,8 @@ __global__ __launch_bounds__(kCbqMaxLevels) void fc_state_kernel(const FcStack<N
 template <int NS>
 __global__ __launch_bounds__(kFcThreads) void fc_output_kernel(const FcStack<NS> st) {
     const FcParams& p = fc_set(st);
-    if ((int)blockIdx.x >= p.G) return;
+    const int nblk = fc_blocks(st);
+    if (NS > 1 && (int)blockIdx.x >= nblk) return;
     __shared__ float s_lev[kCbqMaxLevels];
     const int tid = threadIdx.x, nlev = 1 << p.bits;
     for (int e = tid; e < nlev; e += kFcThreads) s_lev[e] = p.lev[e];
@@ -1408,7 +1416,7 @@ __global__ __launch_bounds__(kFcThreads) void fc_output_kernel(const FcStack<NS>
         const unsigned* __restrict__ c4 = reinterpret_cast<const unsigned*>(p.codes);
         float4* __restrict__ o4 = reinterpret_cast<float4*>(p.v_hat);
         for (long long g0 = (long long)blockIdx.x * kFcThreads * kPer + tid; g0 < ng;
-             g0 += (long long)p.G * kFcThreads * kPer) {
+             g0 += (long long)nblk * kFcThreads * kPer) {
             unsigned cw[kPer];
 #pragma unroll
             for (int j = 0; j < kPer; ++j) {
@@ -1425,7 +1433,7 @@ __global__ __launch_bounds__(kFcThreads) void fc_output_kernel(const FcStack<NS>
         }
         r0 = 4 * ng;
     }
-    for (long long r = r0 + (long long)blockIdx.x * kFcThreads + tid; r < p.m; r += (long long)p.G * kFcThreads)
+    for (long long r = r0 + (long long)blockIdx.x * kFcThreads + tid; r < p.m; r += (long long)nblk * kFcThreads)
         p.v_hat[r] = s_lev[p.codes[r]];
 }
 
