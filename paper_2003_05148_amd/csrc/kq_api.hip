@@ -548,7 +548,7 @@ static void fc_params(FcParams& p, const float* v, const int32_t* w, int64_t cou
     p.thr = (float*)b;
     b += align256(sizeof(float) * nlev);
     p.state = (int*)b;
-    b += align256(sizeof(int) * 4);
+    b += align256(sizeof(int) * 6);
     p.wg_changed = (int*)b;
     b += align256(sizeof(int) * G);
     p.tbl = (unsigned*)b;

@@ -260,12 +260,30 @@ __device__ float code_threshold(int q, const float* lev, int nlev, float vmin, f
     return key_value(hi);
 }
 
+// (level_threshold, below, finds most thresholds without a search)
+//
 // fp32 values v, L with |v|, |L| <= M differ exactly in fp64 when neither is a nonzero
 // value below 2^(e(M) - 29) (e = floor(log2)): their exponents then differ by at most 29,
 // so v - L needs at most 53 bits.  Returns that floor (0 when M is subnormal or zero).
 __device__ __forceinline__ float exact_floor(float M) {
     const int be = (int)((__float_as_uint(M) >> 23) & 255u);
     return be == 0 ? 0.0f : __builtin_ldexpf(1.0f, be - 127 - 29);
+}
+
+__device__ __forceinline__ float fp32_above(double y);
+
+// code_threshold without its search where every fp64 distance involved is exact: levels q and
+// q + 1 differ, they and the two fp32 values around their midpoint are zero or at least
+// exact_floor of the largest magnitude.  The code then changes exactly above the midpoint (which
+// fp64 holds exactly); within the data range only.
+__device__ __forceinline__ float level_threshold(int q, const float* lev, int nlev, float vmin, float vmax) {
+    const float a = lev[q], b = lev[q + 1], fl = exact_floor(fmaxf(fabsf(vmin), fabsf(vmax)));
+    if (a != b) {
+        const float t = fp32_above(0.5 * ((double)a + (double)b));
+        const bool fine = (a == 0.0f || fabsf(a) >= fl) && (b == 0.0f || fabsf(b) >= fl) && fabsf(t) >= 2.0f * fl && fl > 0.0f;
+        if (fine) return t > vmax ? __builtin_inff() : fmaxf(t, vmin);
+    }
+    return code_threshold(q, lev, nlev, vmin, vmax);
 }
 
 // code of x from NLEV - 1 sorted thresholds (s_thr[NLEV - 1] = +inf): every eighth from
@@ -861,12 +879,12 @@ __device__ __forceinline__ int fc_bucket(float x, float lo, float sc) {
 // of them below every value of b) and n = the number inside b; entry b = (c | n << 8,
 // threshold c or +inf).  A value's code is then c plus the count of the n thresholds
 // c .. c + n - 1 at or below it.  Every thread of the workgroup calls it.
-__device__ void set_thresholds(const FcParams& p, const float* s_lev, int nlev, int unsorted, int* s_bad, float vmin,
-                               float vmax) {
+__device__ float level_thresholds(const FcParams& p, const float* s_lev, int nlev, int unsorted, int* s_bad, float vmin,
+                                  float vmax) {
     const int tid = threadIdx.x;
     const double apart = 0x1p-50 * (double)fmaxf(fabsf(vmin), fabsf(vmax));
     // the boundary search costs a few microseconds per round: worth it only for large sets
-    const bool wanted = fc_thr_wanted(p);
+    const bool wanted = p.bucketed || fc_thr_wanted(p);
     if (tid == 0) *s_bad = (unsorted || !wanted) ? 1 : 0;
     __syncthreads();
     if (tid + 1 < nlev && s_lev[tid] != s_lev[tid + 1] && (double)s_lev[tid + 1] - (double)s_lev[tid] < apart) *s_bad = 1;
@@ -874,10 +892,16 @@ __device__ void set_thresholds(const FcParams& p, const float* s_lev, int nlev, 
     const int ok = *s_bad == 0;
     float t = __builtin_inff();
     if (tid < nlev) {
-        t = (ok && tid + 1 < nlev) ? code_threshold(tid, s_lev, nlev, vmin, vmax) : __builtin_inff();
+        t = (ok && tid + 1 < nlev) ? level_threshold(tid, s_lev, nlev, vmin, vmax) : __builtin_inff();
         p.thr[tid] = t;
     }
     if (tid == 0) p.state[3] = ok;
+    return t;
+}
+
+// the bucket table of thresholds t (thread q's threshold q)
+__device__ void threshold_table(const FcParams& p, float t, int nlev, bool ok, float vmin, float vmax) {
+    const int tid = threadIdx.x;
     __shared__ float s_t[kCbqMaxLevels];
     const float sc = (float)kFcBuckets / (vmax - vmin);
     const bool table = ok && vmax > vmin && sc > 0.0f && sc < __builtin_inff();  // the same in every thread
@@ -918,6 +942,12 @@ __device__ void set_thresholds(const FcParams& p, const float* s_lev, int nlev, 
         p.tbl[2 * b + 1] = __float_as_uint(n[i] > 0 ? s_t[c] : __builtin_inff());
         c += n[i];
     }
+}
+
+__device__ void set_thresholds(const FcParams& p, const float* s_lev, int nlev, int unsorted, int* s_bad, float vmin,
+                               float vmax) {
+    const float t = level_thresholds(p, s_lev, nlev, unsorted, s_bad, vmin, vmax);
+    threshold_table(p, t, nlev, *s_bad == 0, vmin, vmax);
 }
 
 // the uniform grid on [min, max]; clears the run state and the running sums
@@ -1473,7 +1503,795 @@ hipError_t launch_fc_sets(const FcParams* sets, int n, hipStream_t s) {
     return hipGetLastError();
 }
 
+// ---- large unweighted sets: rounds on a set partitioned by value ----------------------------
+// A round of scalar k-means needs, per threshold t, how many values lie below t and their exact
+// sum; a pass over the set per round reads 5 bytes a scalar (104 us for 102,760,448 scalars, at
+// the rate of a copy).  So the set is partitioned once, by value, into kFsBuckets buckets of about
+// equal size (splitters: quantiles of a sorted sample), with the exact sum and count of the buckets
+// before each one.  A round then reads only the buckets that a threshold falls into (63 of 1024).
+// The partitioned copy lives in v_hat, which the final pass overwrites; the bucket tables live in
+// the region of the coding launches' partials.
+//   fs_split_kernel    one workgroup: sorts a sample of kFsSample values, splitters, clears counters
+//   fs_hist_kernel     bucket counts, and the set's minimum and maximum
+//   fc_grid_kernel     the first levels and thresholds
+//   fs_base_kernel     one workgroup: where each bucket begins
+//   fs_scatter_kernel  values to their buckets, in tiles of 32768 sorted by bucket in LDS (ranks from
+//                      LDS counters, one reservation per tile and bucket; the order within a bucket
+//                      is free), so that a bucket's share of a tile, about 128 bytes, is written at
+//                      once (straight from the registers: 856 us at 102,760,448 values)
+//   fs_sum_kernel      per bucket the exact sum, minimum and maximum (equal shares of the copy)
+//   fs_prefix_kernel   one workgroup: exact sums of the buckets before each one
+//   per round: fs_cut_kernel (kFsParts workgroups per threshold add its bucket's members below
+//   it), fs_state_kernel (level sums as differences of neighbouring cuts, levels, thresholds)
+//   fs_output_kernel   codes against the final levels and v_hat, from the original values
+// Codes, and with them the end after a round that changed none, depend only on the cuts' counts:
+// {v < t} can only change when its size does.  Sums are exact integers, so levels are those of the
+// coding launches, bit for bit.  When a round's levels allow no thresholds (neighbours closer than
+// 2^-50 of the largest magnitude), this and the rounds after it code every scalar by a full scan
+// of the levels, in the same launches.
+// fc6's 102,760,448 scalars, 30 rounds: 4.43 -> 1.69 ms; 4,096,000: 0.87 -> 0.55 ms (a round: 14 us).
+constexpr int kFsBuckets = 1024;
+constexpr int kFsSample = 4 * kFsBuckets;
+constexpr int kFsThreads = 1024;
+constexpr int kFsPer = 32;                       // values per thread and tile
+constexpr int kFsTile = kFsPer * kFsThreads;
+constexpr int kFsCells = 2048;                   // cells of equal width that index the splitters
+constexpr int kFsParts = 16;                     // workgroups per threshold
+constexpr int kFsCutThreads = 256;
+enum { kFsDone = 0, kFsUpdates = 1, kFsThr = 3, kFsScan = 4, kFsPrev = 5 };  // state words
+
+struct FsView {
+    float* rng;                  // [2] the sample's minimum and maximum: the range of the cells
+    float* spl;                  // [kFsBuckets] bucket b holds spl[b] <= v < spl[b + 1] (spl[0] = -inf)
+    unsigned *cnt, *base, *cur;  // members, first position ([kFsBuckets + 1]), next free position
+    unsigned *kmin, *kmax;       // ordered keys of a bucket's smallest and largest value
+    unsigned long long *dig, *pre;  // [.][kDigits] sum of a bucket, of the buckets before ([kFsBuckets + 1])
+    unsigned long long* cut;     // [levels][kFsParts][kFcCols] a threshold's bucket members below it
+    unsigned* nprev;             // [levels] the previous cuts' counts
+    int* tb;                     // [levels] threshold's bucket to read, or -1 - b: the cut is where bucket b begins
+    size_t bytes;
+};
+__host__ __device__ inline FsView fs_view(const FcParams& p) {
+    FsView f;
+    unsigned char* b = (unsigned char*)p.part;
+    size_t o = 0;
+    const size_t nlev = (size_t)1 << p.bits;
+    auto take = [&](size_t n) {
+        unsigned char* const at = b + o;
+        o += (n + 255) & ~size_t(255);
+        return at;
+    };
+    f.rng = (float*)take(sizeof(float) * 2);
+    f.spl = (float*)take(sizeof(float) * kFsBuckets);
+    f.cnt = (unsigned*)take(sizeof(unsigned) * kFsBuckets);
+    f.base = (unsigned*)take(sizeof(unsigned) * (kFsBuckets + 1));
+    f.cur = (unsigned*)take(sizeof(unsigned) * kFsBuckets);
+    f.kmin = (unsigned*)take(sizeof(unsigned) * kFsBuckets);
+    f.kmax = (unsigned*)take(sizeof(unsigned) * kFsBuckets);
+    f.dig = (unsigned long long*)take(sizeof(long long) * kFsBuckets * kDigits);
+    f.pre = (unsigned long long*)take(sizeof(long long) * (kFsBuckets + 1) * kDigits);
+    f.cut = (unsigned long long*)take(sizeof(long long) * nlev * kFsParts * kFcCols);
+    f.nprev = (unsigned*)take(sizeof(unsigned) * nlev);
+    f.tb = (int*)take(sizeof(int) * nlev);
+    f.bytes = o;
+    return f;
+}
+
+__global__ __launch_bounds__(kFsThreads) void fs_split_kernel(const FcParams p) {
+    __shared__ unsigned s_key[kFsSample];
+    const FsView f = fs_view(p);
+    const int tid = threadIdx.x;
+    for (int i = tid; i < kFsSample; i += kFsThreads)
+        s_key[i] = ordered_key(p.v[(long long)i * (p.m - 1) / (kFsSample - 1)]);
+    for (int e = tid; e < kFsBuckets * kDigits; e += kFsThreads) f.dig[e] = 0ull;
+    f.cnt[tid] = 0u;
+    f.kmin[tid] = 0xffffffffu;
+    f.kmax[tid] = 0u;
+    static_assert(kFsThreads == kFsBuckets, "one thread per bucket");
+    __syncthreads();
+    for (int k = 2; k <= kFsSample; k *= 2)  // bitonic, ascending
+        for (int j = k / 2; j >= 1; j /= 2) {
+            for (int e = tid; e < kFsSample / 2; e += kFsThreads) {
+                const int i = ((e & ~(j - 1)) << 1) | (e & (j - 1)), l = i | j;
+                const unsigned a = s_key[i], b = s_key[l];
+                if ((a > b) == ((i & k) == 0)) {
+                    s_key[i] = b;
+                    s_key[l] = a;
+                }
+            }
+            __syncthreads();
+        }
+    f.spl[tid] = tid == 0 ? -__builtin_inff() : key_value(s_key[tid * (kFsSample / kFsBuckets)]);
+    if (tid < 2) f.rng[tid] = key_value(s_key[tid * (kFsSample - 1)]);
+}
+
+// the splitters and their index in LDS: cell c of equal-width cells over the sample's range (the
+// first and last take what lies outside) holds the
+// number of splitters in lower cells and, << 16, in the cell itself
+struct FsIndex {
+    float spl[kFsBuckets];
+    unsigned cell[kFsCells];
+    unsigned wsum[kFsThreads / kWave];
+};
+__device__ __forceinline__ int fs_cell(float x, float lo, float sc) {
+    return (int)fminf(fmaxf((x - lo) * sc, 0.0f), (float)(kFsCells - 1));  // monotone (NaN to 0)
+}
+__device__ __forceinline__ float fs_scale(const FsView& f) {
+    const float sc = (float)kFsCells / (f.rng[1] - f.rng[0]);
+    return sc > 0.0f && sc < __builtin_inff() ? sc : 0.0f;  // 0: one cell
+}
+__device__ __forceinline__ void fs_index(const FsView& f, FsIndex& s, float lo, float sc) {
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    constexpr int kPer = kFsCells / kFsThreads;
+    const float x = f.spl[tid];
+    s.spl[tid] = x;
+    for (int c = tid; c < kFsCells; c += kFsThreads) s.cell[c] = 0u;
+    __syncthreads();
+    if (tid > 0) atomicAdd(&s.cell[fs_cell(x, lo, sc)], 1u);
+    __syncthreads();
+    unsigned n[kPer], tot = 0u;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        n[i] = s.cell[kPer * tid + i];
+        tot += n[i];
+    }
+    unsigned inc = tot;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const unsigned o = __shfl_up(inc, off);
+        if (lane >= off) inc += o;
+    }
+    if (lane == kWave - 1) s.wsum[wave] = inc;
+    __syncthreads();
+    unsigned at = inc - tot;
+    for (int w = 0; w < wave; ++w) at += s.wsum[w];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        s.cell[kPer * tid + i] = at | (n[i] << 16);
+        at += n[i];
+    }
+    __syncthreads();
+}
+// the buckets of B values: the splitters at or below each, by the index and then a binary search
+// within the cell (the B searches go in step)
+template <int B>
+__device__ __forceinline__ void fs_buckets(const FsIndex& s, const float* x, int* b, float lo, float sc) {
+    int at[B], n[B];
+    int any = 0;
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+        const unsigned e = s.cell[fs_cell(x[i], lo, sc)];
+        at[i] = (int)(e & 0xffffu);
+        n[i] = (int)(e >> 16);
+        any |= n[i];
+    }
+    while (__any(any)) {
+        any = 0;
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            const int h = n[i] >> 1;
+            const bool up = n[i] > 0 && s.spl[min(at[i] + 1 + h, kFsBuckets - 1)] <= x[i];
+            at[i] = up ? at[i] + h + 1 : at[i];
+            n[i] = up ? n[i] - h - 1 : h;
+            any |= n[i];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < B; ++i) b[i] = at[i];
+}
+// this thread's values of a tile (position i of the tile: 4096 u + 4 tid + e from an aligned set,
+// 1024 u + tid otherwise); past the set's end 0, ok false
+template <typename F>
+__device__ __forceinline__ void fs_tile(const FcParams& p, long long t0, float (&x)[kFsPer], F&& ok) {
+    const int tid = threadIdx.x;
+    if ((reinterpret_cast<uintptr_t>(p.v) & 15u) == 0) {
+        const float4* __restrict__ v4 = reinterpret_cast<const float4*>(p.v);
+#pragma unroll
+        for (int u = 0; u < kFsPer / 4; ++u) {
+            const long long r = t0 + 4ll * (u * kFsThreads + tid);
+            float4 w = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (r + 3 < p.m) {
+                w = v4[r >> 2];
+            } else {
+                if (r < p.m) w.x = p.v[r];
+                if (r + 1 < p.m) w.y = p.v[r + 1];
+                if (r + 2 < p.m) w.z = p.v[r + 2];
+            }
+            x[4 * u] = w.x;
+            x[4 * u + 1] = w.y;
+            x[4 * u + 2] = w.z;
+            x[4 * u + 3] = w.w;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ok(4 * u + e, r + e < p.m);
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < kFsPer; ++u) {
+            const long long r = t0 + u * kFsThreads + tid;
+            x[u] = r < p.m ? p.v[r] : 0.0f;
+            ok(u, r < p.m);
+        }
+    }
+}
+
+__global__ __launch_bounds__(kFsThreads) void fs_hist_kernel(const FcParams p) {
+    __shared__ FsIndex s;
+    __shared__ unsigned s_n[kFsBuckets];
+    const FsView f = fs_view(p);
+    const int tid = threadIdx.x;
+    __shared__ float s_lo[kFsThreads / kWave], s_hi[kFsThreads / kWave];
+    const float lo = f.rng[0], sc = fs_scale(f);
+    float vlo = __builtin_inff(), vhi = -__builtin_inff();
+    fs_index(f, s, lo, sc);
+    s_n[tid] = 0u;
+    __syncthreads();
+    for (long long t0 = (long long)blockIdx.x * kFsTile; t0 < p.m; t0 += (long long)gridDim.x * kFsTile) {
+        float x[kFsPer];
+        unsigned have = 0u;
+        fs_tile(p, t0, x, [&](int i, bool h) { have |= h ? 1u << i : 0u; });
+#pragma unroll
+        for (int q = 0; q < kFsPer; q += 8) {
+            int b[8];
+            fs_buckets<8>(s, x + q, b, lo, sc);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (have >> (q + i) & 1u) {
+                    atomicAdd(&s_n[b[i]], 1u);
+                    vlo = fminf(vlo, x[q + i]);
+                    vhi = fmaxf(vhi, x[q + i]);
+                }
+        }
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        vlo = fminf(vlo, __shfl_xor(vlo, off));
+        vhi = fmaxf(vhi, __shfl_xor(vhi, off));
+    }
+    if ((tid & (kWave - 1)) == 0) {
+        s_lo[tid / kWave] = vlo;
+        s_hi[tid / kWave] = vhi;
+    }
+    __syncthreads();
+    if (s_n[tid]) atomicAdd(&f.cnt[tid], s_n[tid]);
+    if (tid == 0) {
+        for (int w = 1; w < kFsThreads / kWave; ++w) {
+            vlo = fminf(vlo, s_lo[w]);
+            vhi = fmaxf(vhi, s_hi[w]);
+        }
+        p.minmax[2 * blockIdx.x] = vlo;
+        p.minmax[2 * blockIdx.x + 1] = vhi;
+    }
+}
+
+__global__ __launch_bounds__(kFsThreads) void fs_base_kernel(const FcParams p) {
+    __shared__ unsigned s_w[kFsThreads / kWave];
+    const FsView f = fs_view(p);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    if (tid == 0) {
+        p.state[kFsScan] = p.state[kFsThr] ? 0 : 1;  // the first levels' thresholds are valid, or not
+        p.state[kFsPrev] = 0;
+    }
+    const unsigned n = f.cnt[tid];
+    unsigned inc = n;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const unsigned o = __shfl_up(inc, off);
+        if (lane >= off) inc += o;
+    }
+    if (lane == kWave - 1) s_w[wave] = inc;
+    __syncthreads();
+    unsigned at = inc - n;
+    for (int w = 0; w < wave; ++w) at += s_w[w];
+    f.base[tid] = at;
+    f.cur[tid] = at;
+    if (tid == kFsBuckets - 1) f.base[kFsBuckets] = at + n;
+}
+
+__global__ __launch_bounds__(kFsThreads) void fs_scatter_kernel(const FcParams p) {
+    __shared__ FsIndex s;
+    __shared__ unsigned s_n[kFsBuckets], s_at[kFsBuckets];  // members in the tile; first place in the set
+    __shared__ unsigned s_first[kFsBuckets];                // first place in the tile
+    __shared__ float s_val[kFsTile];                        // the tile by bucket
+    const FsView f = fs_view(p);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    if (p.state[kFsScan]) return;
+    const float lo = f.rng[0], sc = fs_scale(f);
+    fs_index(f, s, lo, sc);
+    float* __restrict__ out = p.v_hat;
+    for (long long t0 = (long long)blockIdx.x * kFsTile; t0 < p.m; t0 += (long long)gridDim.x * kFsTile) {
+        s_n[tid] = 0u;
+        float x[kFsPer];
+        unsigned have = 0u, br[kFsPer];  // bucket | rank << 10
+        fs_tile(p, t0, x, [&](int i, bool h) { have |= h ? 1u << i : 0u; });
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kFsPer; q += 8) {
+            int b[8];
+            fs_buckets<8>(s, x + q, b, lo, sc);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                br[q + i] = (unsigned)b[i];
+                if (have >> (q + i) & 1u) br[q + i] |= atomicAdd(&s_n[b[i]], 1u) << 10;
+            }
+        }
+        __syncthreads();
+        const unsigned n = s_n[tid];
+        s_at[tid] = n ? atomicAdd(&f.cur[tid], n) : 0u;
+        unsigned inc = n;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const unsigned o = __shfl_up(inc, off);
+            if (lane >= off) inc += o;
+        }
+        if (lane == kWave - 1) s.wsum[wave] = inc;
+        __syncthreads();
+        unsigned at = inc - n;
+        for (int w = 0; w < wave; ++w) at += s.wsum[w];
+        s_first[tid] = at;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kFsPer; ++q)
+            if (have >> q & 1u) s_val[s_first[br[q] & (kFsBuckets - 1)] + (br[q] >> 10)] = x[q];
+        __syncthreads();
+        // half a wave per bucket
+        constexpr int kHalves = 2 * kFsThreads / kWave;
+        const int h = 2 * wave + (lane >> 5), l = lane & 31;
+#pragma unroll 4
+        for (int b = h; b < kFsBuckets; b += kHalves) {
+            const unsigned c = s_n[b], g = s_at[b], v = s_first[b];
+            for (unsigned i = l; i < c; i += 32) out[g + i] = s_val[v + i];
+        }
+        __syncthreads();
+    }
+}
+
+// Exact sum of values in registers: three 32-bit digits from digit d0 on, as 64-bit counts (each
+// value adds less than 2^32 to a digit).  A value with bits below digit d0 goes to the LDS digits.
+struct FsSum {
+    long long a0, a1, a2;
+};
+__device__ __forceinline__ void fs_add(FsSum& s, float x, int d0, unsigned long long* low) {
+    const unsigned u = __float_as_uint(x), e = (u >> 23) & 0xffu;
+    const unsigned mant = (u & 0x7fffffu) | (e ? 0x800000u : 0u);
+    const int sh = (e ? (int)e - 1 : 0) - 32 * d0;  // x 2^149 = mant 2^(sh + 32 d0)
+    if (sh < 0) {
+        if (mant) add_exact(low, x, 1u);
+        return;
+    }
+    const unsigned long long P = (unsigned long long)mant << (sh & 31);
+    long long l = (long long)(P & 0xffffffffull), h = (long long)(P >> 32);
+    if (u >> 31) {
+        l = -l;
+        h = -h;
+    }
+    const bool up = sh >= 32;  // (sh < 64: d0 fits the largest magnitude)
+    s.a0 += up ? 0ll : l;
+    s.a1 += up ? l : h;
+    s.a2 += up ? h : 0ll;
+}
+// the lowest digit for values of magnitude at most M
+__device__ __forceinline__ int fs_digit(float M) {
+    const int e = (int)((__float_as_uint(M) >> 23) & 0xffu);
+    const int d = (e ? e - 1 : 0) >> 5;
+    return d > 0 ? d - 1 : 0;
+}
+// the largest magnitude a member of bucket b can have
+__device__ __forceinline__ float fs_bound(const FcParams& p, const FsView& f, int b) {
+    const float l = b == 0 ? p.range[0] : f.spl[b], h = b == kFsBuckets - 1 ? p.range[1] : f.spl[b + 1];
+    return fmaxf(fabsf(l), fabsf(h));
+}
+
+__global__ __launch_bounds__(kFsCutThreads) void fs_sum_kernel(const FcParams p) {
+    __shared__ unsigned long long s_dig[kDigits];
+    __shared__ unsigned s_lo, s_hi;
+    __shared__ int s_b;
+    const FsView f = fs_view(p);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    if (p.state[kFsScan]) return;
+    const long long len = (p.m + gridDim.x - 1) / gridDim.x;
+    const long long i0 = blockIdx.x * len, i1 = i0 + len < p.m ? i0 + len : p.m;
+    if (i0 >= i1) return;
+    if (tid == 0) {  // the bucket of position i0: the last one that begins at or before it and is not empty
+        int l = 0, h = kFsBuckets;
+        while (h - l > 1) {
+            const int c = (l + h) / 2;
+            if ((long long)f.base[c] <= i0) l = c;
+            else h = c;
+        }
+        s_b = l;
+    }
+    __syncthreads();
+    int b = s_b;
+    for (long long a = i0; a < i1; ++b) {  // (uniform: every thread walks the same buckets)
+        const long long end = f.base[b + 1], z = end < i1 ? end : i1;
+        if (z <= a) continue;
+        if (tid < kDigits) s_dig[tid] = 0ull;
+        if (tid == 0) s_lo = 0xffffffffu, s_hi = 0u;
+        __syncthreads();
+        const int d0 = fs_digit(fs_bound(p, f, b));
+        FsSum s = {0, 0, 0};
+        unsigned lo = 0xffffffffu, hi = 0u;
+        const float* __restrict__ w = p.v_hat;
+        for (long long r = a + tid; r < z; r += 8 * kFsCutThreads) {
+            float x[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) x[q] = r + q * kFsCutThreads < z ? w[r + q * kFsCutThreads] : 0.0f;
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (r + q * kFsCutThreads < z) {
+                    const unsigned k = ordered_key(x[q]);
+                    lo = min(lo, k);
+                    hi = max(hi, k);
+                    fs_add(s, x[q], d0, s_dig);
+                }
+        }
+        s.a0 = wave_sum_i64(s.a0);
+        s.a1 = wave_sum_i64(s.a1);
+        s.a2 = wave_sum_i64(s.a2);
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            lo = min(lo, (unsigned)__shfl_xor((int)lo, off));
+            hi = max(hi, (unsigned)__shfl_xor((int)hi, off));
+        }
+        if (lane == 0) {
+            atomicAdd(&s_dig[d0], (unsigned long long)s.a0);
+            atomicAdd(&s_dig[d0 + 1], (unsigned long long)s.a1);
+            atomicAdd(&s_dig[d0 + 2], (unsigned long long)s.a2);
+            atomicMin(&s_lo, lo);
+            atomicMax(&s_hi, hi);
+        }
+        __syncthreads();
+        if (tid < kDigits && s_dig[tid]) atomicAdd(&f.dig[b * kDigits + tid], s_dig[tid]);
+        if (tid == 0) {
+            atomicMin(&f.kmin[b], s_lo);
+            atomicMax(&f.kmax[b], s_hi);
+        }
+        __syncthreads();
+        a = z;
+    }
+}
+
+// a threshold's place: the bucket whose members have to be looked at, or -1 - b when every member
+// below it lies in a bucket before b and none in b or after
+__device__ __forceinline__ int fs_place(const FsView& f, const float* spl, float t) {
+    if (t == __builtin_inff()) return -1 - kFsBuckets;
+    int l = 0, h = kFsBuckets;  // spl[l] <= t < spl[h]
+    while (h - l > 1) {
+        const int c = (l + h) / 2;
+        if (spl[c] <= t) l = c;
+        else h = c;
+    }
+    if (f.cnt[l] == 0u || t <= key_value(f.kmin[l])) return -1 - l;
+    if (t > key_value(f.kmax[l])) return -1 - (l + 1);
+    return l;
+}
+
+__global__ __launch_bounds__(kFsThreads) void fs_prefix_kernel(const FcParams p) {
+    const FsView f = fs_view(p);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), c = tid / kWave;
+    if (p.state[kFsScan]) return;
+    static_assert(kFsThreads / kWave >= kDigits, "a wave per digit");
+    if (c < kDigits) {
+        constexpr int kPer = kFsBuckets / kWave;  // consecutive buckets per lane
+        unsigned long long n[kPer], tot = 0ull;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) n[i] = f.dig[(lane * kPer + i) * kDigits + c];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) tot += n[i];
+        unsigned long long inc = tot;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const unsigned long long o = __shfl_up(inc, off);
+            if (lane >= off) inc += o;
+        }
+        unsigned long long at = inc - tot;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            f.pre[(lane * kPer + i) * kDigits + c] = at;
+            at += n[i];
+        }
+        if (lane == kWave - 1) f.pre[kFsBuckets * kDigits + c] = at;
+    }
+    const int nlev = 1 << p.bits;
+    if (tid + 1 < nlev) f.tb[tid] = fs_place(f, f.spl, p.thr[tid]);
+}
+
+// workgroups of a full-scan round (their partials take the place of the coding launches')
+__device__ __forceinline__ int fs_scan_blocks(const FcParams& p) { return min(p.G, (1 << p.bits) * kFsParts); }
+
+// kFsParts workgroups per threshold: the count and exact sum of the members of its bucket below it.
+// Full-scan rounds: the first fs_scan_blocks workgroups code every scalar and add up the levels' sums.
+template <int NLEV>
+__global__ __launch_bounds__(kFsCutThreads) void fs_cut_kernel(const FcParams p) {
+    __shared__ unsigned long long s_dig[NLEV * kFcCols];
+    __shared__ float s_lev[NLEV], s_old[NLEV];
+    __shared__ int s_changed;
+    if (fc_done(p)) return;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    if (p.state[kFsScan]) {
+        const int nblk = fs_scan_blocks(p);
+        if ((int)blockIdx.x >= nblk) return;
+        const int prev = p.state[kFsPrev];
+        for (int e = tid; e < NLEV * kFcCols; e += kFsCutThreads) s_dig[e] = 0ull;
+        for (int e = tid; e < NLEV; e += kFsCutThreads) {
+            s_lev[e] = p.lev[e];
+            s_old[e] = p.lev_next[e];  // the thresholds of the round before the first full scan
+        }
+        if (tid == 0) s_changed = prev == 0 ? 1 : 0;
+        __syncthreads();
+        const long long step = (long long)nblk * kFsCutThreads;
+        for (long long r = (long long)blockIdx.x * kFsCutThreads + tid; r < p.m; r += step) {
+            const float x = p.v[r];
+            int c = prev == 2 ? (int)p.codes[r] : 0;
+            if (prev == 1)
+                for (int q = 0; q + 1 < NLEV; ++q) c += s_old[q] <= x ? 1 : 0;
+            const int q = nearest_level_loop(x, s_lev, NLEV);
+            if (q != c) s_changed = 1;
+            p.codes[r] = (uint8_t)q;
+            add_exact(s_dig + q * kFcCols, x, 1u);
+            atomicAdd(&s_dig[q * kFcCols + kDigits], 1ull);
+        }
+        __syncthreads();
+        unsigned long long* part = (unsigned long long*)p.part;  // (the bucket tables are done with)
+        for (int e = tid; e < NLEV * kFcCols; e += kFsCutThreads) part[(size_t)blockIdx.x * NLEV * kFcCols + e] = s_dig[e];
+        if (tid == 0) p.wg_changed[blockIdx.x] = s_changed;
+        return;
+    }
+    const FsView f = fs_view(p);
+    const int q = blockIdx.x / kFsParts, part = blockIdx.x - q * kFsParts;
+    if (q + 1 >= NLEV) return;
+    const int b = f.tb[q];
+    if (b < 0) return;
+    if (tid < kFcCols) s_dig[tid] = 0ull;
+    __syncthreads();
+    const float t = p.thr[q];
+    const int d0 = fs_digit(fs_bound(p, f, b));
+    const long long a = f.base[b], n = (long long)f.base[b + 1] - a;
+    const long long i0 = a + n * part / kFsParts, i1 = a + n * (part + 1) / kFsParts;
+    FsSum s = {0, 0, 0};
+    long long cnt = 0;
+    const float* __restrict__ w = p.v_hat;
+    for (long long r = i0 + tid; r < i1; r += 8 * kFsCutThreads) {
+        float x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = r + u * kFsCutThreads < i1 ? w[r + u * kFsCutThreads] : __builtin_inff();
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (x[u] < t) {
+                ++cnt;
+                fs_add(s, x[u], d0, s_dig);
+            }
+    }
+    s.a0 = wave_sum_i64(s.a0);
+    s.a1 = wave_sum_i64(s.a1);
+    s.a2 = wave_sum_i64(s.a2);
+    cnt = wave_sum_i64(cnt);
+    if (lane == 0) {
+        atomicAdd(&s_dig[d0], (unsigned long long)s.a0);
+        atomicAdd(&s_dig[d0 + 1], (unsigned long long)s.a1);
+        atomicAdd(&s_dig[d0 + 2], (unsigned long long)s.a2);
+        atomicAdd(&s_dig[kDigits], (unsigned long long)cnt);
+    }
+    __syncthreads();
+    if (tid < kFcCols) f.cut[((size_t)q * kFsParts + part) * kFcCols + tid] = s_dig[tid];
+}
+
+__global__ __launch_bounds__(kCbqMaxLevels) void fs_state_kernel(const FcParams p) {
+    __shared__ unsigned long long s_S[kCbqMaxLevels * kFcCols];  // per level boundary, then per level
+    __shared__ float s_lev[kCbqMaxLevels], s_spl[kFsBuckets];
+    __shared__ int s_any, s_unsorted, s_bad;
+    if (fc_done(p)) return;
+    const int tid = threadIdx.x, nlev = 1 << p.bits;
+    const FsView f = fs_view(p);
+    const bool scan = p.state[kFsScan] != 0;
+    if (!scan)
+        for (int e = tid; e < kFsBuckets; e += kCbqMaxLevels) s_spl[e] = f.spl[e];
+    const int updates = p.state[kFsUpdates], prev = p.state[kFsPrev];
+    if (tid == 0) s_any = !scan && prev == 0 ? 1 : 0;
+    if (tid == 0) s_unsorted = 0;
+    __syncthreads();
+    if (scan) {
+        const unsigned long long* part = (const unsigned long long*)p.part;
+        for (int e = tid; e < nlev * kFcCols; e += kCbqMaxLevels) {
+            unsigned long long t = 0ull;
+#pragma unroll 8
+            for (int w = 0; w < fs_scan_blocks(p); ++w) t += part[(size_t)w * nlev * kFcCols + e];
+            s_S[e] = t;
+        }
+        for (int w = tid; w < fs_scan_blocks(p); w += kCbqMaxLevels)
+            if (p.wg_changed[w]) s_any = 1;
+        __syncthreads();
+    } else {
+        // the sums and counts below each threshold (the last boundary: the whole set)
+        for (int e = tid; e < nlev * kFcCols; e += kCbqMaxLevels) {
+            const int q = e / kFcCols, c = e - q * kFcCols;
+            const int tb = q + 1 < nlev ? f.tb[q] : -1 - kFsBuckets;
+            const int b = tb < 0 ? -1 - tb : tb;
+            unsigned long long t = c == kDigits ? (unsigned long long)f.base[b] : f.pre[(size_t)b * kDigits + c];
+            if (tb >= 0) {
+                unsigned long long part[kFsParts];
+#pragma unroll
+                for (int w = 0; w < kFsParts; ++w) part[w] = f.cut[((size_t)q * kFsParts + w) * kFcCols + c];
+#pragma unroll
+                for (int w = 0; w < kFsParts; ++w) t += part[w];
+            }
+            s_S[e] = t;
+        }
+        __syncthreads();
+        if (tid + 1 < nlev) {
+            const unsigned n = (unsigned)s_S[tid * kFcCols + kDigits];
+            if (prev != 0 && f.nprev[tid] != n) s_any = 1;
+            f.nprev[tid] = n;
+        }
+        __syncthreads();
+    }
+    const bool update = s_any && updates < p.iters;
+    if (!update) {  // (uniform)
+        if (tid == 0) p.state[kFsDone] = 1;
+        return;
+    }
+    if (tid < nlev) {
+        unsigned long long S[kDigits], W = s_S[tid * kFcCols + kDigits];
+#pragma unroll
+        for (int c = 0; c < kDigits; ++c) S[c] = s_S[tid * kFcCols + c];
+        if (!scan && tid > 0) {  // a level's members lie between its two boundaries
+            W -= s_S[(tid - 1) * kFcCols + kDigits];
+#pragma unroll
+            for (int c = 0; c < kDigits; ++c) S[c] -= s_S[(tid - 1) * kFcCols + c];
+        }
+        const float L = W > 0ull ? (float)(digits_to_double(S) / (double)W) : p.lev[tid];
+        s_lev[tid] = L;
+        p.lev[tid] = L;
+        if (!scan) p.lev_next[tid] = p.thr[tid];  // the thresholds of the codes so far
+    }
+    __syncthreads();
+    if (tid + 1 < nlev && !(s_lev[tid] <= s_lev[tid + 1])) s_unsorted = 1;
+    __syncthreads();
+    const float t = level_thresholds(p, s_lev, nlev, s_unsorted, &s_bad, p.range[0], p.range[1]);
+    __syncthreads();
+    const bool ok = s_bad == 0;
+    if (!scan && ok && tid + 1 < nlev) f.tb[tid] = fs_place(f, s_spl, t);
+    if (tid == 0) {
+        p.state[kFsUpdates] = updates + 1;
+        p.state[2] = s_unsorted;
+        if (!scan && !ok) p.state[kFsScan] = 1;
+        p.state[kFsPrev] = scan ? 2 : 1;
+    }
+}
+
+// the bucket table of the final thresholds
+__global__ __launch_bounds__(kCbqMaxLevels) void fs_table_kernel(const FcParams p) {
+    const int tid = threadIdx.x, nlev = 1 << p.bits;
+    if (p.state[kFsScan]) return;
+    threshold_table(p, tid < nlev ? p.thr[tid] : __builtin_inff(), nlev, true, p.range[0], p.range[1]);
+}
+
+// the codes of the final levels, v_hat and the levels
+template <int NLEV>
+__global__ __launch_bounds__(kFcThreads) void fs_output_kernel(const FcParams p) {
+    __shared__ float s_lev[NLEV], s_thr[NLEV];
+    __shared__ uint2 s_tbl[kFcBuckets];
+    const int tid = threadIdx.x;
+    for (int e = tid; e < NLEV; e += kFcThreads) {
+        s_lev[e] = p.lev[e];
+        s_thr[e] = p.thr[e];
+    }
+    const bool scan = p.state[kFsScan] != 0;
+    const float blo = p.range[0], bsc = p.range[3];
+    const bool table = bsc > 0.0f;
+    if (!scan && table)
+        for (int e = tid; e < kFcBuckets; e += kFcThreads) s_tbl[e] = make_uint2(p.tbl[2 * e], p.tbl[2 * e + 1]);
+    __syncthreads();
+    if (blockIdx.x == 0) {
+        for (int e = tid; e < NLEV; e += kFcThreads) p.levels_out[e] = s_lev[e];
+        if (tid == 0 && p.rounds_out) *p.rounds_out = p.state[kFsUpdates];
+    }
+    auto code = [&](float x) {
+        if (scan) return nearest_level_loop(x, s_lev, NLEV);
+        int c = 0, n = NLEV - 1;
+        if (table) {
+            const uint2 e = s_tbl[fc_bucket(x, blo, bsc)];
+            c = (int)(e.x & 255u);
+            n = (int)(e.x >> 8);
+            if (n <= 1) return c + (__uint_as_float(e.y) <= x ? 1 : 0);
+        }
+        int q = c;
+        for (int j = 0; j < n; ++j) q += s_thr[c + j] <= x ? 1 : 0;
+        return q;
+    };
+    long long r0 = 0;  // scalars from here on: one at a time
+    if (((reinterpret_cast<uintptr_t>(p.v) | reinterpret_cast<uintptr_t>(p.v_hat)) & 15u) == 0 &&
+        (reinterpret_cast<uintptr_t>(p.codes) & 3u) == 0) {
+        constexpr int kPer = 4;  // groups of four scalars in flight
+        const long long ng = p.m >> 2;
+        const float4* __restrict__ v4 = reinterpret_cast<const float4*>(p.v);
+        unsigned* __restrict__ c4 = reinterpret_cast<unsigned*>(p.codes);
+        float4* __restrict__ o4 = reinterpret_cast<float4*>(p.v_hat);
+        for (long long g0 = (long long)blockIdx.x * kFcThreads * kPer + tid; g0 < ng;
+             g0 += (long long)gridDim.x * kFcThreads * kPer) {
+            float4 x[kPer];
+#pragma unroll
+            for (int j = 0; j < kPer; ++j) {
+                const long long g = g0 + (long long)j * kFcThreads;
+                x[j] = g < ng ? v4[g] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            }
+#pragma unroll
+            for (int j = 0; j < kPer; ++j) {
+                const long long g = g0 + (long long)j * kFcThreads;
+                if (g >= ng) continue;
+                const int a = code(x[j].x), b = code(x[j].y), c = code(x[j].z), d = code(x[j].w);
+                c4[g] = (unsigned)a | (unsigned)b << 8 | (unsigned)c << 16 | (unsigned)d << 24;
+                o4[g] = make_float4(s_lev[a], s_lev[b], s_lev[c], s_lev[d]);
+            }
+        }
+        r0 = 4 * ng;
+    }
+    for (long long r = r0 + (long long)blockIdx.x * kFcThreads + tid; r < p.m; r += (long long)gridDim.x * kFcThreads) {
+        const int q = code(p.v[r]);
+        p.codes[r] = (uint8_t)q;
+        p.v_hat[r] = s_lev[q];
+    }
+}
+
+// whether a set takes the partitioned rounds: unweighted, with a v_hat of its own for the
+// partitioned copy, room for the tables, and large enough (or thresholds asked for).  Below, the
+// 0.13 ms of the partition cost more than the coding launches' rounds: 300,000 scalars 492 us by
+// the exact search; 1,000,000 scalars 680 us, partitioned 515.
+constexpr long long kFsMin = 3ll << 18;
+bool fs_usable(const FcParams& p) {
+    if (p.w != nullptr || p.v_hat == nullptr || p.thr_mode == 1 || (p.thr_mode == 0 && p.m < kFsMin) || p.bits < 3) return false;
+    const char *v = (const char*)p.v, *o = (const char*)p.v_hat;
+    const long long nb = p.m * (long long)sizeof(float);
+    if (v < o + nb && o < v + nb) return false;  // in place
+    return fs_view(p).bytes <= sizeof(long long) * (size_t)fc_grid(p.m) * ((size_t)1 << p.bits) * kFcCols;
+}
+
+hipError_t launch_fs_quantize(const FcParams& set, hipStream_t s) {
+    FcParams p = set;
+    p.G = fc_grid(p.m);
+    p.bucketed = 1;
+    FcStack<1> st;
+    st.L[0] = p;
+    const int nlev = 1 << p.bits;
+    const long long tiles = (p.m + kFsTile - 1) / kFsTile;
+    const int Gt = (int)(tiles < 256 ? tiles : 256), Gs = 2 * p.G;
+    hipError_t e = hipSuccess;
+    auto run = [&](auto kernel, int grid, int threads, const auto& arg) {
+        if (e != hipSuccess) return;
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, s, arg);
+        e = hipGetLastError();
+    };
+    run(fs_split_kernel, 1, kFsThreads, p);
+    run(fs_hist_kernel, Gt, kFsThreads, p);
+    st.L[0].G = Gt;  // the minima and maxima are those of fs_hist_kernel's workgroups
+    run(fc_grid_kernel<1>, 1, kCbqMaxLevels, st);
+    run(fs_base_kernel, 1, kFsThreads, p);
+    run(fs_scatter_kernel, Gt, kFsThreads, p);
+    run(fs_sum_kernel, Gs, kFsCutThreads, p);
+    run(fs_prefix_kernel, 1, kFsThreads, p);
+    auto rounds = [&](auto lev) {
+        constexpr int NLEV = decltype(lev)::value;
+        for (int r = 0; r < p.iters; ++r) {
+            run(fs_cut_kernel<NLEV>, nlev * kFsParts, kFsCutThreads, p);
+            run(fs_state_kernel, 1, kCbqMaxLevels, p);
+        }
+        run(fs_table_kernel, 1, kCbqMaxLevels, p);
+        run(fs_output_kernel<NLEV>, p.G, kFcThreads, p);
+    };
+    switch (p.bits) {
+        case 3: rounds(std::integral_constant<int, 8>{}); break;
+        case 4: rounds(std::integral_constant<int, 16>{}); break;
+        case 5: rounds(std::integral_constant<int, 32>{}); break;
+        case 6: rounds(std::integral_constant<int, 64>{}); break;
+        case 7: rounds(std::integral_constant<int, 128>{}); break;
+        case 8: rounds(std::integral_constant<int, 256>{}); break;
+        default: return hipErrorInvalidValue;
+    }
+    return e;
+}
+
 hipError_t launch_fc_quantize(const FcParams* sets, int n, hipStream_t s) {
+    if (n == 1 && fs_usable(sets[0])) return launch_fs_quantize(sets[0], s);
     return n == 1 ? launch_fc_sets<1>(sets, 1, s) : launch_fc_sets<KQ_MAX_STACK>(sets, n, s);
 }
 

@@ -326,10 +326,12 @@ struct FcParams {
     float* lev;            // [levels] current levels
     float* lev_next;       // [levels] candidate levels
     float* thr;            // [levels] code thresholds of the current levels (last one +inf)
-    int* state;            // [0] converged, [1] level updates made, [2] levels unsorted, [3] thresholds valid
+    int* state;            // [0] converged, [1] level updates made, [2] levels unsorted, [3] thresholds valid;
+                           // partitioned rounds: [4] full scans, [5] how the last codes are known
     int* wg_changed;       // [grid] a code changed in the workgroup
     unsigned* tbl;         // [kFcBuckets][2] bucket table of the thresholds (range[3] > 0: valid)
     int G;                 // workgroups of this set (fc_grid(m); filled by the launcher)
+    int bucketed;          // rounds on the set partitioned by value (filled by the launcher)
 };
 // threshold rounds: the data range is cut into this many buckets of equal width; a scalar's
 // bucket gives the count of the thresholds below the bucket and the first one inside it
@@ -338,7 +340,7 @@ int fc_grid(long long m);
 inline size_t fc_ws_bytes(long long m, int bits) {
     const size_t G = (size_t)fc_grid(m), nlev = (size_t)1 << bits;
     return align256(sizeof(float) * (3 * G + 4)) + align256(sizeof(long long) * G * nlev * 12) +
-           align256(sizeof(long long) * nlev * 12) + 3 * align256(sizeof(float) * nlev) + align256(sizeof(int) * 4) +
+           align256(sizeof(long long) * nlev * 12) + 3 * align256(sizeof(float) * nlev) + align256(sizeof(int) * 6) +
            align256(sizeof(int) * G) + align256(sizeof(unsigned) * 2 * kFcBuckets);
 }
 // n sets (at most KQ_MAX_STACK) in one sequence of launches: one unweighted set, or weighted

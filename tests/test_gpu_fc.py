@@ -153,3 +153,58 @@ def test_fc_threshold_rounds_with_a_partial_last_wave(groups):
         b = kq.kq_quantize_scalars(vd, 6, iters, search="exact")
         for x, y, name in zip(a, b, ["codes", "levels", "v_hat", "rounds"]):
             assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), (groups, iters, name)
+
+
+@pytest.mark.parametrize("kind", ["symmetric", "late", "integers", "constant", "two", "heavy", "outliers", "tiny"])
+@pytest.mark.parametrize("bits", [6, 8])
+def test_fc_partitioned_rounds(kind, bits):
+    """Rounds on the set partitioned by value (thresholds asked for, v_hat given): against the
+    oracle at sizes with a ragged last tile; data whose levels come closer to zero, and to each
+    other, than thresholds allow ("symmetric": from the first update; "late": after several), so
+    that the rounds go over to full scans; few distinct values (buckets of one value, empty
+    buckets); values at every scale."""
+    m = 70001
+    rng = np.random.default_rng(bits)
+    if kind == "symmetric":
+        v = rng.choice([-1.0, -1e-30, 1e-30, 1.0], m).astype(np.float32)
+    elif kind == "late":
+        v = (rng.standard_normal(m) * 0.1).astype(np.float32)
+        v[::2] = (rng.choice([-1.0, 1.0], v[::2].size) * 10.0 ** rng.uniform(-40, -25, v[::2].size)).astype(np.float32)
+        v = np.concatenate([v, -v])[:m]
+    elif kind == "two":
+        v = rng.choice([0.25, 0.75], m).astype(np.float32)
+    else:
+        v = data(kind, m, 3)
+    for iters in (0, 2, 30):
+        oc, ol, ov, orr = oracle.quantize_scalars(v, bits, iters)
+        for u in (dev(v), dev(np.concatenate([[np.float32(0)], v]))[1:]):   # aligned to 16 bytes, and not
+            codes, levels, v_hat, rounds = kq.kq_quantize_scalars(u, bits, iters, search="thresholds")
+            assert np.array_equal(host(levels).view(np.uint32), ol.view(np.uint32)), (kind, bits, iters)
+            assert np.array_equal(host(codes), oc), (kind, bits, iters)
+            assert np.array_equal(host(v_hat).view(np.uint32), ov.view(np.uint32)), (kind, bits, iters)
+            assert int(host(rounds)[0]) == orr, (kind, bits, iters)
+
+
+def test_fc_without_and_in_place_of_v_hat():
+    """Without v_hat there is no room for the partitioned copy, in place it would overwrite the
+    set: both take the coding launches, with the same codes and levels."""
+    m = 9 * 100003
+    v = dev(data("normal", m, 8))
+    a = kq.kq_quantize_scalars(v, 6, 30)
+    b = kq.kq_quantize_scalars(v, 6, 30, want_v_hat=False)
+    w = v.clone()
+    c = kq.kq_quantize_scalars(w, 6, 30, v_hat=w)
+    for x, y in ((a, b), (a, c)):
+        assert torch.equal(x[0], y[0]) and torch.equal(x[1], y[1]) and torch.equal(x[3], y[3])
+    assert torch.equal(a[2], w)
+
+
+@pytest.mark.parametrize("bits", [3, 4, 5, 7])
+@pytest.mark.parametrize("kind", ["normal", "heavy", "integers", "tiny"])
+def test_fc_partitioned_rounds_of_other_widths(kind, bits):
+    v = dev(data(kind, 786432 + 5, bits))                     # partitioned without being asked for
+    for iters in (3, 30):
+        a = kq.kq_quantize_scalars(v, bits, iters)
+        b = kq.kq_quantize_scalars(v, bits, iters, search="exact")
+        for x, y, name in zip(a, b, ["codes", "levels", "v_hat", "rounds"]):
+            assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), (kind, bits, iters, name)
