@@ -179,11 +179,12 @@ struct Screen {
     int slot;
 };
 
-// the staged codebook (npair pairs of tiles) screened against a unit's kernels
+// the staged codebook (npair pairs of tiles; FULL: kPairs) screened against a unit's kernels
+template <bool FULL>
 __device__ __forceinline__ Screen scan(const u32x4 (&bop)[2][2], const u32x4* s_a, int npair, int lane) {
-    asm volatile("" : "+v"(lane));  // the operands are read here, not kept from one unit to the next
     float best[2][16];
-    if (npair == kPairs) {
+    if constexpr (FULL) {
+        asm volatile("" : "+v"(lane));  // the operands are read here, not kept from one unit to the next
         u32x4 a[2][2];
         lds_a(a, s_a, 0, lane);
         f32x16 p[2];
@@ -193,25 +194,30 @@ __device__ __forceinline__ Screen scan(const u32x4 (&bop)[2][2], const u32x4* s_
         for (int u = 1; u + 1 < kPairs; ++u) scan_pair<false, true>(best, p, a, bop, s_a, u, lane);
         scan_pair<false, false>(best, p, a, bop, s_a, kPairs - 1, lane);
     } else {  // one pair after another (the pipelined form as a loop, or unrolled per size, spills)
-        u32x4 a[2][2], an[2][2];
-        lds_a(a, s_a, 0, lane);
-        lds_a(an, s_a, min(1, npair - 1), lane);  // the next pair's operands
-        f32x16 p[2], q[2];
-        score_pair(p, a, bop[0]);
-        score_pair(q, a, bop[1]);
-        fold_pair<true>(best[0], p);
-        fold_pair<true>(best[1], q);
+        u32x4 an[2][2];
+        {
+            u32x4 a[2][2];
+            lds_a(a, s_a, 0, lane);
+            lds_a(an, s_a, min(1, npair - 1), lane);  // the next pair's operands
+            f32x16 acc[2][2];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) score_pair(acc[r], a, bop[r]);
+#pragma unroll
+            for (int r = 0; r < 2; ++r) fold_pair<true>(best[r], acc[r]);
+        }
 #pragma unroll 1
-        for (int v = 1; v < npair; ++v) {
+        for (int tp = 1; tp < npair; ++tp) {
+            u32x4 a[2][2];
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
                 for (int kk = 0; kk < 2; ++kk) a[u][kk] = an[u][kk];
-            lds_a(an, s_a, min(v + 1, npair - 1), lane);
-            score_pair(p, a, bop[0]);
-            score_pair(q, a, bop[1]);
-            fold_pair<false>(best[0], p);
-            fold_pair<false>(best[1], q);
+            lds_a(an, s_a, min(tp + 1, npair - 1), lane);  // the next pair's operands
+            f32x16 acc[2][2];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) score_pair(acc[r], a, bop[r]);
+#pragma unroll
+            for (int r = 0; r < 2; ++r) fold_pair<false>(best[r], acc[r]);
         }
     }
     Screen s;
@@ -284,9 +290,11 @@ __device__ __forceinline__ void stage(const float* __restrict__ C, int k, int kp
     }
 }
 
-template <bool FUSED, int KMAX>
+// FULL: every codebook of the launch has kFuseMaxK entries once padded (the pipelined scan; in one
+// kernel with the loop over any number of pairs it costs 16 registers and a spill)
+template <bool FUSED, int KMAX, bool FULL>
 __global__ __launch_bounds__(kAssignWaves * kWave, 1) void assign_kernel(const StackParams p) {
-    static_assert(!FUSED || KMAX == kFuseMaxK, "the sums' histogram holds kFuseMaxK entries");
+    static_assert((!FUSED && !FULL) || KMAX == kFuseMaxK, "the sums' histogram holds kFuseMaxK entries");
     __shared__ u32x4 s_a[KMAX / 32 * 2 * kWave];    // [tile][k-step][lane] A operands
     __shared__ f32x4 s_c[KMAX * kRowFloats / 4];    // fp32 rows of the entries
     __shared__ unsigned long long s_sum[FUSED ? kFuseMaxK * kDim : 1];  // fused: member sums
@@ -307,7 +315,7 @@ __global__ __launch_bounds__(kAssignWaves * kWave, 1) void assign_kernel(const S
     if (ub >= u_end) return;
 
     const int kpad = (k + 63) & ~63;
-    if (kpad > KMAX) return;  // (the host sends larger codebooks to the other kernel)
+    if (kpad > KMAX || (FULL && kpad != kFuseMaxK)) return;  // (the host chooses the kernel accordingly)
 
     float xo[kDim];  // this lane's kernel
     load_kernel(L, ub + wave, lane, xo);
@@ -350,7 +358,7 @@ __global__ __launch_bounds__(kAssignWaves * kWave, 1) void assign_kernel(const S
             rd = take ? d : rd;
             bt = take ? tq : bt;
         };
-        if (kpad == kFuseMaxK) {  // 256 entries: constant tile numbers
+        if (FULL || kpad == kFuseMaxK) {  // 256 entries: constant tile numbers
 #pragma unroll
             for (int tq = 0; tq < 2 * kPairs; ++tq) rescore(tq);
         } else {
@@ -431,7 +439,7 @@ __global__ __launch_bounds__(kAssignWaves * kWave, 1) void assign_kernel(const S
         load_kernel(L, nxt < u_end ? nxt : cur, lane, xn);
         u32x4 bop[2][2];
         make_b(bop, xo);
-        settle(cur, xo, scan(bop, s_a, kpad >> 6, lane));
+        settle(cur, xo, scan<FULL>(bop, s_a, kpad >> 6, lane));
 #pragma unroll
         for (int d = 0; d < kDim; ++d) xo[d] = xn[d];
         cur = nxt;
@@ -494,8 +502,12 @@ int assign_partition(const int* units, const int* ks, int nlayers, int* g) {
 constexpr int kAssignMaxK = 1024;
 
 hipError_t launch_assign(const StackParams& p, hipStream_t s, bool fused, hipEvent_t start, hipEvent_t stop) {
-    int kmax = 0;
-    for (int l = 0; l < p.nlayers; ++l) kmax = p.L[l].k > kmax ? p.L[l].k : kmax;
+    int kmax = 0, kmin = KQ_MAX_K;
+    for (int l = 0; l < p.nlayers; ++l) {
+        kmax = p.L[l].k > kmax ? p.L[l].k : kmax;
+        kmin = p.L[l].k < kmin ? p.L[l].k : kmin;
+    }
+    const bool full = kmin > kFuseMaxK - 64 && kmax <= kFuseMaxK;
     if (fused && kmax > kFuseMaxK) return hipErrorInvalidValue;
     if (kmax > kAssignMaxK) return launch_assign_large(p, s, start, stop);
     const dim3 g(p.assign_grid), b(kAssignWaves * kWave);
@@ -506,8 +518,9 @@ hipError_t launch_assign(const StackParams& p, hipStream_t s, bool fused, hipEve
             hipLaunchKernelGGL(kernel, g, b, 0, s, p);
         return hipGetLastError();
     };
-    if (fused) return launch(assign_kernel<true, kFuseMaxK>);
-    return kmax <= kFuseMaxK ? launch(assign_kernel<false, kFuseMaxK>) : launch(assign_kernel<false, kAssignMaxK>);
+    if (fused) return full ? launch(assign_kernel<true, kFuseMaxK, true>) : launch(assign_kernel<true, kFuseMaxK, false>);
+    if (kmax > kFuseMaxK) return launch(assign_kernel<false, kAssignMaxK, false>);
+    return full ? launch(assign_kernel<false, kFuseMaxK, true>) : launch(assign_kernel<false, kFuseMaxK, false>);
 }
 
 hipError_t launch_assign_finish(const StackParams& p, hipStream_t s) {
