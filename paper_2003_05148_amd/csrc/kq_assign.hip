@@ -295,6 +295,8 @@ __device__ __forceinline__ void stage(const float* __restrict__ C, int k, int kp
 template <bool FUSED, int KMAX, bool FULL>
 __global__ __launch_bounds__(kAssignWaves * kWave, 1) void assign_kernel(const StackParams p) {
     static_assert((!FUSED && !FULL) || KMAX == kFuseMaxK, "the sums' histogram holds kFuseMaxK entries");
+    constexpr bool kSplit = KMAX > kFuseMaxK;       // waves may share a unit
+    __shared__ u32x4 s_x[kSplit ? kAssignWaves * kWave : 1];  // their summaries
     __shared__ u32x4 s_a[KMAX / 32 * 2 * kWave];    // [tile][k-step][lane] A operands
     __shared__ f32x4 s_c[KMAX * kRowFloats / 4];    // fp32 rows of the entries
     __shared__ unsigned long long s_sum[FUSED ? kFuseMaxK * kDim : 1];  // fused: member sums
@@ -344,7 +346,8 @@ __global__ __launch_bounds__(kAssignWaves * kWave, 1) void assign_kernel(const S
 
     // unit lu (kernel x of this lane) ends: the winning slot rescored in fp32, the guard, the
     // kernels that it could not settle, the outputs
-    auto settle = [&](int lu, const float (&x)[kDim], const Screen& s) {
+    // (part, parts: the winning slot counts only every parts-th pair of tiles, from pair `part` on)
+    auto settle = [&](int lu, const float (&x)[kDim], const Screen& s, int part, int parts) {
         const int i = lu * kWave + lane;
         const bool valid = i < n;
         // exact fp32 rescoring of the winning slot's entries, in increasing index order
@@ -358,12 +361,20 @@ __global__ __launch_bounds__(kAssignWaves * kWave, 1) void assign_kernel(const S
             rd = take ? d : rd;
             bt = take ? tq : bt;
         };
-        if (FULL || kpad == kFuseMaxK) {  // 256 entries: constant tile numbers
+        if (FULL || (!kSplit && kpad == kFuseMaxK)) {  // 256 entries: constant tile numbers
 #pragma unroll
             for (int tq = 0; tq < 2 * kPairs; ++tq) rescore(tq);
-        } else {
+        } else if (!kSplit || parts == 1) {
 #pragma unroll 4
             for (int tq = 0; tq < kpad >> 5; ++tq) rescore(tq);
+        } else {  // (the part differs from lane to lane: a pair past the end is taken for the last, again)
+            const int npair = kpad >> 6, most = (npair + parts - 1) / parts;
+#pragma unroll 2
+            for (int i = 0; i < most; ++i) {
+                const int v = part + i * parts;
+                rescore(2 * (v < npair ? v : part));
+                rescore(2 * (v < npair ? v : part) + 1);
+            }
         }
         const int rj = bt < 0 ? 0x7fffffff : s.slot + 32 * bt;
 
@@ -418,6 +429,56 @@ __global__ __launch_bounds__(kAssignWaves * kWave, 1) void assign_kernel(const S
         }
     };
 
+    // A run of few units leaves waves idle: several waves then share a unit, each screens every
+    // parts-th pair of tiles, and the unit's first wave merges their summaries (in LDS) and settles
+    // it: a group is then the entries of one slot in one wave's pairs.  4096 kernels, k = 600: 8.4
+    // -> 7.0 us.
+    if constexpr (kSplit) {
+        const int npair = kpad >> 6, parts = min(kAssignWaves / (u_end - ub), npair);
+        if (parts > 1) {
+            __syncthreads();
+            const int uw = wave / parts, part = wave - uw * parts, lu = ub + uw;  // uniform over the wave
+            Screen s = {kMaxFloat, kMaxFloat, 0};
+            if (lu < u_end) {
+                load_kernel(L, lu, lane, xo);
+                u32x4 bop[2][2];
+                make_b(bop, xo);
+                float best[2][16];
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) best[r][q] = kMaxFloat;
+#pragma unroll 1
+                for (int v = part; v < npair; v += parts) {
+                    u32x4 a[2][2];
+                    lds_a(a, s_a, v, lane);
+                    f32x16 p0[2], p1[2];
+                    score_pair(p0, a, bop[0]);
+                    score_pair(p1, a, bop[1]);
+                    fold_pair<false>(best[0], p0);
+                    fold_pair<false>(best[1], p1);
+                }
+                top2_slots(best, s.m1, s.m2, s.slot);
+                s_x[wave * kWave + lane] = u32x4{__float_as_uint(s.m1), __float_as_uint(s.m2), (unsigned)s.slot, 0u};
+            }
+            __syncthreads();
+            if (lu < u_end && part == 0) {
+                int win = 0;
+                for (int q = 1; q < parts; ++q) {
+                    const u32x4 o = s_x[(wave + q) * kWave + lane];
+                    const float o1 = __uint_as_float(o[0]), o2 = __uint_as_float(o[1]);
+                    const float mx = __builtin_amdgcn_fmed3f(s.m1, o1, __builtin_inff());  // the larger
+                    s.m2 = min3f(s.m2, o2, mx);
+                    const bool lt = o1 < s.m1;
+                    s.m1 = lt ? o1 : s.m1;
+                    s.slot = lt ? (int)o[2] : s.slot;
+                    win = lt ? q : win;
+                }
+                settle(lu, xo, s, win, parts);
+            }
+            return;
+        }
+    }
     // Each wave starts with unit ub + wave.  With the small units of up to 256 entries it then takes
     // the next unit from an LDS counter, so that a wave its SIMD serves less often takes fewer
     // units; longer units are dealt out in turn (262,144 kernels at k = 512, 16 units for 12 waves:
@@ -439,7 +500,7 @@ __global__ __launch_bounds__(kAssignWaves * kWave, 1) void assign_kernel(const S
         load_kernel(L, nxt < u_end ? nxt : cur, lane, xn);
         u32x4 bop[2][2];
         make_b(bop, xo);
-        settle(cur, xo, scan<FULL>(bop, s_a, kpad >> 6, lane));
+        settle(cur, xo, scan<FULL>(bop, s_a, kpad >> 6, lane), 0, 1);
 #pragma unroll
         for (int d = 0; d < kDim; ++d) xo[d] = xn[d];
         cur = nxt;

@@ -34,6 +34,9 @@ constexpr int kUpdateMinKernelsPerBlock = 1024;
 constexpr int kUpdateTargetBlocks = 256;
 constexpr int kUpdateLdsMaxK = 768;     // LDS histogram [768][9] int64 + [768] u32
 constexpr int kFinishEntries = 16;  // codebook entries per finishing workgroup
+// updates whose layers all have at most this many kernels (and k <= kUpdateSmallK) take one launch
+constexpr int kUpdateSmallN = 16384;
+constexpr int kUpdateSmallK = 4096;
 constexpr size_t kUpdatePartialBudget = size_t(1) << 24;  // bytes of partials per layer above 768 entries
 
 inline int update_ranges(int32_t k) { return (k + kUpdateLdsMaxK - 1) / kUpdateLdsMaxK; }
@@ -284,6 +287,8 @@ hipError_t launch_assign_large(const StackParams& p, hipStream_t s, hipEvent_t s
 hipError_t launch_assign_finish(const StackParams& p, hipStream_t s);
 hipError_t launch_update(const StackParams& p, hipStream_t s);
 hipError_t launch_update_finish(const StackParams& p, hipStream_t s);
+// the update in one launch (small layers; the distortion from the assignment's partials)
+hipError_t launch_update_small(const StackParams& p, hipStream_t s);
 hipError_t launch_fill_zero(void* ws, size_t bytes, hipStream_t s);
 // the block maxima of |x| (or |g|) and, with `with_shift`, each layer's shift and non-finite
 // flag; without it the next launch that forms sums derives the shift (StackParams::derive_shift)

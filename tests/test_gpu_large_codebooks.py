@@ -139,3 +139,46 @@ def test_wide_codebooks_share_their_launches(bits):
         for x, y, z in zip(a, b, c):
             assert torch.equal(x.view(torch.uint8), y.view(torch.uint8))
             assert torch.equal(x.view(torch.uint8), z.view(torch.uint8))
+
+
+# one launch updates layers of at most 16384 kernels and 4096 entries; above, the general path
+SMALL_UPDATES = [[(1, 1)], [(16384, 300)], [(16385, 300)], [(16384, 4096)], [(4096, 4097)], [(8191, 1000), (100, 17), (700, 513)]]
+
+
+@pytest.mark.parametrize("shape", SMALL_UPDATES)
+def test_update_of_small_layers(shape):
+    """Counts, means and distortion after an assignment, through the stack calls and through a fit
+    (bit for bit the separate update's), with entries that have no kernels."""
+    layers = [layer(n, k, 40 + i) for i, (n, k) in enumerate(shape)]
+    st = kq.Stack([dev(X) for X, _ in layers], [dev(C) for _, C in layers], iters=2)
+    kq.kq_assign_stack(st, distortion=False)
+    before = [c.clone() for c in st.C]
+    kq.kq_update_stack(st, dist_slot=1, distortion_from_assign=True)
+    for i, (X, C) in enumerate(layers):
+        idx = host(st.idx[i])
+        assert np.array_equal(idx, oracle.assign(X, C)["idx"])
+        Cn, z, _ = kq.kq_update(st.X[i], st.idx[i], before[i])       # sums by the general path
+        assert torch.equal(st.counts[i], z) and torch.equal(st.C[i], Cn), shape[i]
+        oC, oz = oracle.update(X, idx, C)
+        assert np.array_equal(host(st.counts[i]), oz)
+        err = np.abs(host(st.C[i]).astype(np.float64) - oC).max(axis=1)
+        assert (err <= 1e-5 * np.maximum(np.abs(oC).max(axis=1), 1e-300)).all(), shape[i]
+        if C.shape[0] <= X.shape[0]:
+            gC, gi, gz, gJ = kq.kq_fit_layer(st.X[i], dev(C), 2)
+            D = dev(C)
+            for _ in range(2):
+                a = kq.kq_assign(st.X[i], D)[0]
+                D = kq.kq_update(st.X[i], a, D)[0]
+            a, _, J = kq.kq_assign(st.X[i], D)
+            assert torch.equal(gC, D) and torch.equal(gi, a) and torch.equal(gJ[-1:], J), shape[i]
+            assert np.array_equal(host(gz), np.bincount(host(a), minlength=C.shape[0]))
+
+
+# runs of few units: one to six per workgroup, several waves per unit, and k at the edges
+@pytest.mark.parametrize("n,k", [(64, 300), (100, 257), (4096, 600), (64 * 256 * 2, 700), (64 * 256 * 3 + 5, 1024),
+                                 (64 * 256 * 7, 300), (1, 1024)])
+def test_assign_several_waves_per_unit(n, k):
+    X = laplace(n, n + k)
+    check_assign(X, synth.random_codebook_state(X, k, k), (n, k))
+    C = X[np.random.default_rng(n).integers(0, n, k)].copy()       # copies: exact ties
+    check_assign(X, C, (n, k, "copies"))
