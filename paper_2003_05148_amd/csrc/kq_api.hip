@@ -145,6 +145,22 @@ bool fusable(const kq_layer* layers, int32_t l0, int32_t l1) {
     return true;
 }
 
+// Fits whose codebooks could be fused but whose layers are small take the assignment without sums,
+// in which several waves share a unit, and the one-launch update: each workgroup of a fused launch
+// has at most a few units, but stores a whole histogram for the finish to read.  It needs codebooks
+// of more than 128 entries (an update workgroup owns 16 of them) with at most 64 kernels per entry
+// (LDS atomics on the same sums), and runs short enough to share.  20 rounds, k = 256: 4096 kernels
+// 247 us fused, 231; 16384: 348, 303; 16 layers of 4096: 281, 270; but 8 layers of 16384: 292, 357,
+// and 4096 kernels at k = 100: 224, 239.
+bool fit_small(const kq_layer* layers, int32_t l0, int32_t l1) {
+    int units = 0;
+    for (int32_t l = l0; l < l1; ++l) {
+        if (layers[l].n > kUpdateSmallN || layers[l].k <= 128 || layers[l].n > 64ll * layers[l].k) return false;
+        units += assign_units(layers[l].n);
+    }
+    return units <= kAssignGridMax * (kAssignWaves / 3);
+}
+
 // The assignment's workgroups over layers [l0, l1): each layer gets its own workgroups
 // (assign_partition), which split its units evenly; a layer's fused partials are those of
 // its workgroups.  For every layer: its first workgroup and their number; returns the grid.
@@ -266,7 +282,8 @@ kq_status run_fit(const kq_layer* layers, int32_t n_layers, int32_t iters, unsig
             }
             init = nullptr;
         }
-        const bool fused = fusable(layers, l0, l1);  // the member sums come with the assignment
+        // the member sums come with the assignment, or (small layers) with the one-launch update
+        const bool fused = fusable(layers, l0, l1) && !fit_small(layers, l0, l1);
         // with fused sums nothing reads a round's indices but the last round's: the rounds
         // before it store none (nor best distances)
         kq_layer inner[KQ_MAX_STACK];

@@ -580,7 +580,12 @@ hipError_t launch_assign(const StackParams& p, hipStream_t s, bool fused, hipEve
         return hipGetLastError();
     };
     if (fused) return full ? launch(assign_kernel<true, kFuseMaxK, true>) : launch(assign_kernel<true, kFuseMaxK, false>);
-    if (kmax > kFuseMaxK) return launch(assign_kernel<false, kAssignMaxK, false>);
+    bool few = true;  // workgroups of few units: their waves share them
+    for (int l = 0; l < p.nlayers; ++l) {
+        const int w = (l + 1 < p.nlayers ? p.wg_begin[l + 1] : p.assign_grid) - p.wg_begin[l];
+        few &= (p.L[l].nunits + w - 1) / w <= kAssignWaves / 2;
+    }
+    if (kmax > kFuseMaxK || few) return launch(assign_kernel<false, kAssignMaxK, false>);
     return full ? launch(assign_kernel<false, kFuseMaxK, true>) : launch(assign_kernel<false, kFuseMaxK, false>);
 }
 
