@@ -40,7 +40,7 @@
 // gets ceil(U_l / floor(t / w_l)) workgroups, w_l the cost of one of its units and t the
 // smallest cost per workgroup for which the total fits, and its U_l units are spread
 // evenly over them, so a workgroup works within one layer.  This file's kernel serves the
-// launches whose codebooks all have at most 256 entries (kq_assign_large.hip the others): the
+// launches whose codebooks all have at most kAssignMaxK entries (kq_assign_large.hip the others): the
 // codebook is split and staged once in LDS, in the MFMA A-operand order [tile][k-step][lane][8 x
 // bf16] (one conflict-free ds_read_b128 per MFMA operand) and as fp32 rows for the slot
 // rescoring, and the unit loop has no barrier.  Each lane splits its own kernel; the B operands

@@ -1,5 +1,5 @@
 // Device code shared by the two assignment kernels (kq_assign.hip: every codebook of at most
-// 256 entries; kq_assign_large.hip: any codebook).
+// 1024 entries; kq_assign_large.hip: any codebook).
 #pragma once
 
 #include "kq_internal.h"

@@ -1,6 +1,6 @@
 // Assignment against codebooks of any size (Sec. 3.1, Eq. 1), used whenever a launch holds a
-// codebook of more than 256 entries.  The result is the one of kq_assign.hip, bit for bit: the
-// argmin of the fp32 squared distances, ties to the lowest index.
+// codebook of more than 1024 entries (kAssignMaxK).  The result is the one of kq_assign.hip, bit
+// for bit: the argmin of the fp32 squared distances, ties to the lowest index.
 //
 // With a large codebook the screening product is the work, and the matrix cores' power bounds it
 // (a pair of 32-entry tiles against 64 kernels: 115 ns on a SIMD with zeros for operands, 160 ns
