@@ -16,7 +16,8 @@
 // update_kernel: one launch covers every layer of a stack.  A layer's kernels are cut
 // into chunks and its codebook into ranges of at most 768 entries; a workgroup of 1024
 // threads takes one (chunk, range) pair: it reads the chunk's indices, one 36-byte row per
-// thread and step (consecutive lanes, consecutive rows, two steps in flight), loads the
+// thread and step (consecutive lanes, consecutive rows, two steps in flight; with several
+// ranges it lists the range's members first: add_listed), loads the
 // rows whose entry lies in its range and adds them to a private LDS histogram of the range
 // ([768][9] int64 sums + [768] counts at most, ds_add_u64), then stores the histogram
 // into the chunk's partial ([chunks][k][10] int64).  Chunk sizes give about one workgroup
@@ -104,8 +105,75 @@ __device__ __forceinline__ void add_rows(const UpdateCtx& c, const float* __rest
     }
 }
 
+// One of several ranges: few rows of a wave lie in it, so the members are listed first and their
+// values then added densely, one per lane (consecutive lanes read a member's row).  kTileKernels
+// indices at a time; list entries are the kernel's place in the tile | entry of the range << 16.
+// Whole passes, a row per thread and step before: the VGG-16 stack with k = 60 .. 1088 3452 us,
+// listed 3309; the ResNet-18 stack with k = 609 .. 7679 12.61 and 12.20 ms; 1,048,576 kernels, k =
+// 4096, 10 rounds 2918 and 2835 us.  The gathers of 36-byte pieces bound it.
+constexpr int kTileBatch = 4;
+constexpr int kTileKernels = kTileBatch * kUpdateThreads;
+__device__ __forceinline__ void add_listed(const UpdateCtx& c, const float* __restrict__ X, const int32_t* __restrict__ idx,
+                                           int i0, int i1, unsigned* s_list, unsigned* s_n) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    int j[kTileBatch];
+    auto load = [&](int t0) {
+#pragma unroll
+        for (int u = 0; u < kTileBatch; ++u) {
+            const int o = u * kUpdateThreads + tid;
+            j[u] = o < i1 - t0 ? idx[t0 + o] : -1;
+        }
+    };
+    load(i0);
+    int par = 0;  // the counter of this tile; the other one is cleared for the next
+    for (int t0 = i0; t0 < i1; par ^= 1) {  // (uniform; the counters start at zero)
+        if (tid == 0) s_n[par ^ 1] = 0u;
+        unsigned before[kTileBatch], total = 0u;
+        bool in[kTileBatch];
+#pragma unroll
+        for (int u = 0; u < kTileBatch; ++u) {
+            in[u] = (unsigned)(j[u] - c.j0) < (unsigned)c.kr;
+            const unsigned long long m = __ballot(in[u]);
+            before[u] = total + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+            total += (unsigned)__popcll(m);
+        }
+        unsigned at = 0u;
+        if (lane == 0 && total) at = atomicAdd(&s_n[par], total);
+        at = (unsigned)__builtin_amdgcn_readfirstlane((int)at);
+#pragma unroll
+        for (int u = 0; u < kTileBatch; ++u)
+            if (in[u]) {
+                const unsigned jr = (unsigned)(j[u] - c.j0);
+                s_list[at + before[u]] = (unsigned)(u * kUpdateThreads + tid) | jr << 16;
+                atomicAdd(&c.s_cnt[jr], 1u);
+            }
+        const float* __restrict__ Xt = X + (size_t)t0 * kDim;
+        const bool more = i1 - t0 > kTileKernels;
+        if (more) load(t0 + kTileKernels);  // in flight while this tile is added
+        __syncthreads();
+        const unsigned nv = s_n[par] * kDim;
+        for (unsigned v0 = (unsigned)tid; v0 < nv; v0 += kTileBatch * kUpdateThreads) {
+            float x[kTileBatch];
+            unsigned e[kTileBatch];
+#pragma unroll
+            for (int u = 0; u < kTileBatch; ++u) {
+                const unsigned v = min(v0 + u * kUpdateThreads, nv - 1u), m = v / kDim, q = v - m * kDim, w = s_list[m];
+                x[u] = Xt[(w & 0xffffu) * kDim + q];
+                e[u] = (w >> 16) * kDim + q;
+            }
+#pragma unroll
+            for (int u = 0; u < kTileBatch; ++u)
+                if (v0 + u * kUpdateThreads < nv) atomicAdd(&c.s_sum[e[u]], fixed_bits(x[u], c.scale));
+        }
+        if (!more) break;
+        t0 += kTileKernels;
+        __syncthreads();  // the list is free
+    }
+}
+
 __global__ __launch_bounds__(kUpdateThreads) void update_kernel(const StackParams p) {
     extern __shared__ unsigned long long s_dyn[];  // [krange][9] sums, then [krange] u32 counts
+    __shared__ unsigned s_list[kTileKernels], s_n[2];
     __shared__ double s_wd[kUpdateThreads / kWave];
     __shared__ unsigned s_mx;
 
@@ -137,6 +205,7 @@ __global__ __launch_bounds__(kUpdateThreads) void update_kernel(const StackParam
 
     for (int e = tid; e < c.kr * kDim; e += kUpdateThreads) c.s_sum[e] = 0ull;
     for (int e = tid; e < c.kr; e += kUpdateThreads) c.s_cnt[e] = 0u;
+    if (tid < 2) s_n[tid] = 0u;
     __syncthreads();
 
     double dacc = 0.0;
@@ -146,8 +215,10 @@ __global__ __launch_bounds__(kUpdateThreads) void update_kernel(const StackParam
         add_rows<false, false>(c, L.X, L.idx, i0 + tid, i1, dacc);
     else if (L.ranges == 1)
         add_rows<true, false>(c, L.X, L.idx, i0 + tid, i1, dacc);
-    else
+    else if (c.want_dist)  // (the distances are added in the order of the rows)
         add_rows<true, true>(c, L.X, L.idx, i0 + tid, i1, dacc);
+    else
+        add_listed(c, L.X, L.idx, i0, i1, s_list, s_n);
 
     __syncthreads();
     unsigned long long* __restrict__ out = (unsigned long long*)L.hist + ((size_t)chunk * k + c.j0) * 10;

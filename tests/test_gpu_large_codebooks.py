@@ -182,3 +182,21 @@ def test_assign_several_waves_per_unit(n, k):
     check_assign(X, synth.random_codebook_state(X, k, k), (n, k))
     C = X[np.random.default_rng(n).integers(0, n, k)].copy()       # copies: exact ties
     check_assign(X, C, (n, k, "copies"))
+
+
+@pytest.mark.parametrize("n,k", [(4095, 769), (4097, 1537), (8193, 7679), (40001, 2305)])
+def test_update_over_several_ranges(n, k):
+    """The listed sums (no distortion asked for) and the sums in the order of the rows are the same
+    integers: codebooks and counts bit for bit, with indices to ignore, an entry that holds every
+    other kernel and entries without any."""
+    X, C = layer(n, k, 70 + k)
+    idx = synth.random_indices(n, k, 71)
+    idx[::2] = k - 1
+    idx[1:40:4], idx[3:40:4] = -1, k
+    idx[idx == 5] = 6
+    rows = kq.kq_update(dev(X), dev(idx), dev(C))
+    listed = kq.kq_update(dev(X), dev(idx), dev(C), with_distortion=False)
+    want = np.bincount(idx[(idx >= 0) & (idx < k)], minlength=k)
+    assert np.array_equal(host(listed[1]), want) and np.array_equal(host(rows[1]), want)
+    assert np.array_equal(host(listed[0]).view(np.uint32), host(rows[0]).view(np.uint32))
+    assert np.array_equal(host(listed[0])[want == 0], C[want == 0])
