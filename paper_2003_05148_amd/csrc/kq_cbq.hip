@@ -1529,7 +1529,7 @@ hipError_t launch_fc_sets(const FcParams* sets, int n, hipStream_t s) {
 // coding launches, bit for bit.  When a round's levels allow no thresholds (neighbours closer than
 // 2^-50 of the largest magnitude), this and the rounds after it code every scalar by a full scan
 // of the levels, in the same launches.
-// fc6's 102,760,448 scalars, 30 rounds: 4.43 -> 1.69 ms; 4,096,000: 0.87 -> 0.55 ms (a round: 14 us).
+// fc6's 102,760,448 scalars, 30 rounds: 4.43 -> 1.60 ms; 4,096,000: 0.87 -> 0.48 ms.
 constexpr int kFsBuckets = 1024;
 constexpr int kFsSample = 4 * kFsBuckets;
 constexpr int kFsThreads = 1024;
@@ -1953,7 +1953,8 @@ __global__ __launch_bounds__(kFsCutThreads) void fs_sum_kernel(const FcParams p)
 
 // a threshold's place: the bucket whose members have to be looked at, or -1 - b when every member
 // below it lies in a bucket before b and none in b or after
-__device__ __forceinline__ int fs_place(const FsView& f, const float* spl, float t) {
+__device__ __forceinline__ int fs_place(const float* spl, const unsigned* cnt, const unsigned* kmin, const unsigned* kmax,
+                                        float t) {
     if (t == __builtin_inff()) return -1 - kFsBuckets;
     int l = 0, h = kFsBuckets;  // spl[l] <= t < spl[h]
     while (h - l > 1) {
@@ -1961,8 +1962,8 @@ __device__ __forceinline__ int fs_place(const FsView& f, const float* spl, float
         if (spl[c] <= t) l = c;
         else h = c;
     }
-    if (f.cnt[l] == 0u || t <= key_value(f.kmin[l])) return -1 - l;
-    if (t > key_value(f.kmax[l])) return -1 - (l + 1);
+    if (cnt[l] == 0u || t <= key_value(kmin[l])) return -1 - l;
+    if (t > key_value(kmax[l])) return -1 - (l + 1);
     return l;
 }
 
@@ -1993,7 +1994,7 @@ __global__ __launch_bounds__(kFsThreads) void fs_prefix_kernel(const FcParams p)
         if (lane == kWave - 1) f.pre[kFsBuckets * kDigits + c] = at;
     }
     const int nlev = 1 << p.bits;
-    if (tid + 1 < nlev) f.tb[tid] = fs_place(f, f.spl, p.thr[tid]);
+    if (tid + 1 < nlev) f.tb[tid] = fs_place(f.spl, f.cnt, f.kmin, f.kmax, p.thr[tid]);
 }
 
 // workgroups of a full-scan round (their partials take the place of the coding launches')
@@ -2006,9 +2007,15 @@ __global__ __launch_bounds__(kFsCutThreads) void fs_cut_kernel(const FcParams p)
     __shared__ unsigned long long s_dig[NLEV * kFcCols];
     __shared__ float s_lev[NLEV], s_old[NLEV];
     __shared__ int s_changed;
-    if (fc_done(p)) return;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    if (p.state[kFsScan]) {
+    const FsView f = fs_view(p);
+    const int q = blockIdx.x / kFsParts, part = blockIdx.x - q * kFsParts;
+    // one batch of loads: the run's state, this threshold and its place
+    const int done = p.state[kFsDone], scan = p.state[kFsScan], b = f.tb[q];
+    const float t = p.thr[q];
+    asm volatile("" ::"s"(done), "s"(scan), "s"(b), "s"(t));
+    if (done) return;
+    if (scan) {
         const int nblk = fs_scan_blocks(p);
         if ((int)blockIdx.x >= nblk) return;
         const int prev = p.state[kFsPrev];
@@ -2037,14 +2044,9 @@ __global__ __launch_bounds__(kFsCutThreads) void fs_cut_kernel(const FcParams p)
         if (tid == 0) p.wg_changed[blockIdx.x] = s_changed;
         return;
     }
-    const FsView f = fs_view(p);
-    const int q = blockIdx.x / kFsParts, part = blockIdx.x - q * kFsParts;
-    if (q + 1 >= NLEV) return;
-    const int b = f.tb[q];
-    if (b < 0) return;
+    if (q + 1 >= NLEV || b < 0) return;
     if (tid < kFcCols) s_dig[tid] = 0ull;
     __syncthreads();
-    const float t = p.thr[q];
     const int d0 = fs_digit(fs_bound(p, f, b));
     const long long a = f.base[b], n = (long long)f.base[b + 1] - a;
     const long long i0 = a + n * part / kFsParts, i1 = a + n * (part + 1) / kFsParts;
@@ -2076,51 +2078,69 @@ __global__ __launch_bounds__(kFsCutThreads) void fs_cut_kernel(const FcParams p)
     if (tid < kFcCols) f.cut[((size_t)q * kFsParts + part) * kFcCols + tid] = s_dig[tid];
 }
 
-__global__ __launch_bounds__(kCbqMaxLevels) void fs_state_kernel(const FcParams p) {
+// One workgroup: the launch is a chain of memory round trips, so everything whose address is
+// known at the start is loaded in one batch (the tables that place the new thresholds among
+// them), and only the sums before a threshold's bucket wait for the bucket's number.  With a
+// load after each result, 256 threads: 8.9 us; a whole 4,096,000-scalar call 552 us, now 480.
+__global__ __launch_bounds__(kFsThreads) void fs_state_kernel(const FcParams p) {
     __shared__ unsigned long long s_S[kCbqMaxLevels * kFcCols];  // per level boundary, then per level
     __shared__ float s_lev[kCbqMaxLevels], s_spl[kFsBuckets];
+    __shared__ unsigned s_cnt[kFsBuckets], s_kmin[kFsBuckets], s_kmax[kFsBuckets];
     __shared__ int s_any, s_unsorted, s_bad;
-    if (fc_done(p)) return;
     const int tid = threadIdx.x, nlev = 1 << p.bits;
     const FsView f = fs_view(p);
+    const int done = p.state[kFsDone], updates = p.state[kFsUpdates], prev = p.state[kFsPrev];
     const bool scan = p.state[kFsScan] != 0;
-    if (!scan)
-        for (int e = tid; e < kFsBuckets; e += kCbqMaxLevels) s_spl[e] = f.spl[e];
-    const int updates = p.state[kFsUpdates], prev = p.state[kFsPrev];
+    // (after full scans these hold other data, in bounds all the same, and are not used)
+    const float spl = f.spl[tid];
+    const unsigned cnt = f.cnt[tid], kmin = f.kmin[tid], kmax = f.kmax[tid];
+    auto cut_of = [&](int e, int& tb, unsigned long long (&part)[kFsParts]) {  // e = boundary, column
+        const int q = e / kFcCols, c = e - q * kFcCols;
+        tb = q + 1 < nlev ? f.tb[q] : -1 - kFsBuckets;
+#pragma unroll
+        for (int w = 0; w < kFsParts; ++w) part[w] = f.cut[((size_t)q * kFsParts + w) * kFcCols + c];
+    };
+    int tb0 = -1;
+    unsigned long long part0[kFsParts];
+#pragma unroll
+    for (int w = 0; w < kFsParts; ++w) part0[w] = 0ull;
+    if (tid < nlev * kFcCols) cut_of(tid, tb0, part0);
+    const unsigned nprev = tid < nlev ? f.nprev[tid] : 0u;
+    asm volatile("" ::"v"(spl), "v"(cnt), "v"(kmin), "v"(kmax), "v"(tb0), "v"(nprev), "v"(part0[0]), "v"(part0[kFsParts - 1]));
+    if (done) return;
+    s_spl[tid] = spl;
+    s_cnt[tid] = cnt;
+    s_kmin[tid] = kmin;
+    s_kmax[tid] = kmax;
     if (tid == 0) s_any = !scan && prev == 0 ? 1 : 0;
     if (tid == 0) s_unsorted = 0;
     __syncthreads();
     if (scan) {
         const unsigned long long* part = (const unsigned long long*)p.part;
-        for (int e = tid; e < nlev * kFcCols; e += kCbqMaxLevels) {
+        for (int e = tid; e < nlev * kFcCols; e += kFsThreads) {
             unsigned long long t = 0ull;
 #pragma unroll 8
             for (int w = 0; w < fs_scan_blocks(p); ++w) t += part[(size_t)w * nlev * kFcCols + e];
             s_S[e] = t;
         }
-        for (int w = tid; w < fs_scan_blocks(p); w += kCbqMaxLevels)
+        for (int w = tid; w < fs_scan_blocks(p); w += kFsThreads)
             if (p.wg_changed[w]) s_any = 1;
         __syncthreads();
     } else {
         // the sums and counts below each threshold (the last boundary: the whole set)
-        for (int e = tid; e < nlev * kFcCols; e += kCbqMaxLevels) {
-            const int q = e / kFcCols, c = e - q * kFcCols;
-            const int tb = q + 1 < nlev ? f.tb[q] : -1 - kFsBuckets;
-            const int b = tb < 0 ? -1 - tb : tb;
+        for (int e = tid; e < nlev * kFcCols; e += kFsThreads) {
+            if (e != tid) cut_of(e, tb0, part0);
+            const int c = e % kFcCols, b = tb0 < 0 ? -1 - tb0 : tb0;
             unsigned long long t = c == kDigits ? (unsigned long long)f.base[b] : f.pre[(size_t)b * kDigits + c];
-            if (tb >= 0) {
-                unsigned long long part[kFsParts];
+            if (tb0 >= 0)
 #pragma unroll
-                for (int w = 0; w < kFsParts; ++w) part[w] = f.cut[((size_t)q * kFsParts + w) * kFcCols + c];
-#pragma unroll
-                for (int w = 0; w < kFsParts; ++w) t += part[w];
-            }
+                for (int w = 0; w < kFsParts; ++w) t += part0[w];
             s_S[e] = t;
         }
         __syncthreads();
         if (tid + 1 < nlev) {
             const unsigned n = (unsigned)s_S[tid * kFcCols + kDigits];
-            if (prev != 0 && f.nprev[tid] != n) s_any = 1;
+            if (prev != 0 && nprev != n) s_any = 1;
             f.nprev[tid] = n;
         }
         __syncthreads();
@@ -2150,7 +2170,7 @@ __global__ __launch_bounds__(kCbqMaxLevels) void fs_state_kernel(const FcParams 
     const float t = level_thresholds(p, s_lev, nlev, s_unsorted, &s_bad, p.range[0], p.range[1]);
     __syncthreads();
     const bool ok = s_bad == 0;
-    if (!scan && ok && tid + 1 < nlev) f.tb[tid] = fs_place(f, s_spl, t);
+    if (!scan && ok && tid + 1 < nlev) f.tb[tid] = fs_place(s_spl, s_cnt, s_kmin, s_kmax, t);
     if (tid == 0) {
         p.state[kFsUpdates] = updates + 1;
         p.state[2] = s_unsorted;
@@ -2273,7 +2293,7 @@ hipError_t launch_fs_quantize(const FcParams& set, hipStream_t s) {
         constexpr int NLEV = decltype(lev)::value;
         for (int r = 0; r < p.iters; ++r) {
             run(fs_cut_kernel<NLEV>, nlev * kFsParts, kFsCutThreads, p);
-            run(fs_state_kernel, 1, kCbqMaxLevels, p);
+            run(fs_state_kernel, 1, kFsThreads, p);
         }
         run(fs_table_kernel, 1, kCbqMaxLevels, p);
         run(fs_output_kernel<NLEV>, p.G, kFcThreads, p);
