@@ -246,8 +246,12 @@ constexpr int kFinishDirectK = kFinishDirectWgs * kFinishEntries;  // 256
 constexpr int kFinishThreads = kFinishEntries * 10 * kFinishGroups;  // 640
 static_assert(kFinishThreads >= kSumThreads, "the distortion sum uses the first kSumThreads threads");
 
+// GROUPS 6: six threads share a value's partials, 16 entries per workgroup.  GROUPS 1: one thread
+// per value, 96 entries per workgroup.
+template <int GROUPS>
 __global__ __launch_bounds__(kFinishThreads) void update_finish_kernel(const StackParams p) {
-    __shared__ unsigned long long s_S[kFinishGroups][kFinishEntries * 10];
+    constexpr int kE = kFinishEntries * kFinishGroups / GROUPS;  // entries per workgroup
+    __shared__ unsigned long long s_S[GROUPS][kE * 10];
     __shared__ double s_w[kSumThreads / kWave];
     const int b = blockIdx.x;
     // The launch is short, and every dependent load of the arguments is a memory round trip.
@@ -279,7 +283,7 @@ __global__ __launch_bounds__(kFinishThreads) void update_finish_kernel(const Sta
     }
     const int lt = direct ? ld : find_layer(p, b);  // the layer
     const int li = lt;
-    if (!direct) {  // layer and entry range from the table: each layer owns ceil(k / kFinishEntries) workgroups
+    if (!direct) {  // layer and entry range from the table: each layer owns ceil(k / kE) workgroups
         const DevLayer& Lt = p.L[lt];
         k = Lt.k;
         nb = Lt.nchunks;
@@ -291,9 +295,9 @@ __global__ __launch_bounds__(kFinishThreads) void update_finish_kernel(const Sta
         C_old = Lt.C_old;
     }
     const DevLayer& L = p.L[li];
-    const int j0 = (b - ub) * kFinishEntries;
+    const int j0 = (b - ub) * kE;
     const int tid = threadIdx.x;
-    const int g = tid / (kFinishEntries * 10), v = tid - g * (kFinishEntries * 10);
+    const int g = tid / (kE * 10), v = tid - g * (kE * 10);
     const int j = j0 + v / 10, d = v - 10 * (v / 10);
     // the entry's old value and the layer's shift, in flight with the partials
     const bool writes_c = g == 0 && j < k && d < kDim && (flags & kFlagCountsOnly) == 0;
@@ -308,13 +312,13 @@ __global__ __launch_bounds__(kFinishThreads) void update_finish_kernel(const Sta
     if (j < k) {
         const size_t stride = (size_t)k * 10;
         const unsigned long long* hp = h + (size_t)j * 10 + d;
-        // partials g, g + 8, ...: kFinishBatch loads in flight at a time
+        // partials g, g + GROUPS, ...: kFinishBatch loads in flight at a time
 #pragma unroll 1
-        for (int q0 = g; q0 < nb; q0 += kFinishBatch * kFinishGroups) {
+        for (int q0 = g; q0 < nb; q0 += kFinishBatch * GROUPS) {
             unsigned long long v[kFinishBatch];
 #pragma unroll
             for (int r = 0; r < kFinishBatch; ++r) {
-                const int q = q0 + r * kFinishGroups;
+                const int q = q0 + r * GROUPS;
                 v[r] = q < nb ? hp[(size_t)q * stride] : 0ull;
             }
 #pragma unroll
@@ -326,7 +330,7 @@ __global__ __launch_bounds__(kFinishThreads) void update_finish_kernel(const Sta
     if (g == 0 && j < k) {
         unsigned long long S = 0, z = 0;  // wrapping sums
 #pragma unroll
-        for (int q = 0; q < kFinishGroups; ++q) {
+        for (int q = 0; q < GROUPS; ++q) {
             S += s_S[q][v];
             z += s_S[q][(v / 10) * 10 + 9];
         }
@@ -526,21 +530,36 @@ hipError_t launch_update(const StackParams& p, hipStream_t s) {
     return hipGetLastError();
 }
 
-// the finishing launch numbers its workgroups per layer: ceil(k / 4) each
+// The finishing launch numbers its workgroups per layer: ceil(k / entries) each.  Where 16 entries
+// a workgroup would make more workgroups than the chip holds twice over and a value has few
+// partials, one thread adds them all and a workgroup takes 96 entries (the ResNet-18 stack with
+// k = 609 .. 7679, 3462 workgroups of 960 threads: 18.7 us a launch; the whole compression pass
+// 12.00 ms, now 11.67; a single k = 4096 layer, 256 workgroups, 6.9 us, stays with six threads).
+constexpr int kFinishManyWgs = 1024, kFinishFewPartials = 2 * kFinishBatch;
 hipError_t launch_update_finish(const StackParams& p, hipStream_t s) {
     StackParams q = p;
     bool direct = true;  // every codebook fits kFinishDirectWgs workgroups
     for (int l = 0; l < q.nlayers; ++l) direct &= q.L[l].k <= kFinishDirectK;
     q.finish_direct = direct ? 1 : 0;
+    int wgs = 0, most = 0;
+    for (int l = 0; l < q.nlayers; ++l) {
+        wgs += (q.L[l].k + kFinishEntries - 1) / kFinishEntries;
+        most = q.L[l].nchunks > most ? q.L[l].nchunks : most;
+    }
+    const bool wide = wgs > kFinishManyWgs && most <= kFinishFewPartials;  // (then not direct: that has at most 256)
+    const int per = wide ? kFinishEntries * kFinishGroups : kFinishEntries;
     int blk = 0;
     for (int l = 0; l < q.nlayers; ++l) {
         q.L[l].unit_begin = blk;
-        blk += direct ? kFinishDirectWgs : (q.L[l].k + kFinishEntries - 1) / kFinishEntries;
+        blk += direct ? kFinishDirectWgs : (q.L[l].k + per - 1) / per;
     }
     q.total_units = blk;  // followed by one workgroup per layer for the distortion
     set_unit_table(q);
     // nunits keeps the number of update workgroups (partials to add)
-    hipLaunchKernelGGL(update_finish_kernel, dim3(blk + q.nlayers), dim3(kFinishThreads), 0, s, q);
+    if (wide)
+        hipLaunchKernelGGL(update_finish_kernel<1>, dim3(blk + q.nlayers), dim3(kFinishThreads), 0, s, q);
+    else
+        hipLaunchKernelGGL(update_finish_kernel<kFinishGroups>, dim3(blk + q.nlayers), dim3(kFinishThreads), 0, s, q);
     return hipGetLastError();
 }
 

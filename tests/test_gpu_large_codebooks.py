@@ -200,3 +200,17 @@ def test_update_over_several_ranges(n, k):
     assert np.array_equal(host(listed[1]), want) and np.array_equal(host(rows[1]), want)
     assert np.array_equal(host(listed[0]).view(np.uint32), host(rows[0]).view(np.uint32))
     assert np.array_equal(host(listed[0])[want == 0], C[want == 0])
+
+
+def test_update_finish_of_many_entries():
+    """Three large codebooks finished in one launch (96 entries a workgroup) and one by one (16)."""
+    sizes = [(8193, 7679), (9000, 5000), (20001, 6001)]
+    made = [layer(n, k, 80 + i) for i, (n, k) in enumerate(sizes)]
+    st = kq.Stack([dev(X) for X, _ in made], [dev(C) for _, C in made])
+    for i, (n, k) in enumerate(sizes):
+        st.idx[i].copy_(dev(synth.random_indices(n, k, 90 + i)))
+    alone = [kq.kq_update(st.X[i], st.idx[i], st.C[i], with_distortion=False)[:2] for i in range(3)]
+    kq.kq_update_stack(st)
+    for i in range(3):
+        assert np.array_equal(host(st.counts[i]), host(alone[i][1]))
+        assert np.array_equal(host(st.C[i]).view(np.uint32), host(alone[i][0]).view(np.uint32))
