@@ -319,12 +319,12 @@ __device__ __forceinline__ int code_from_thresholds(float x, const float* s_thr,
     return 8 * c + (f4 ? 4 : 0) + (f2 ? 2 : 0) + (f1 ? 1 : 0);
 }
 
-// ---- codebooks of at most kCbqFastMax scalars whose values all meet the exactness condition
+// ---- codebooks of at most kCbqExactMax scalars whose values all meet the exactness condition
 // (finite, no nonzero magnitude below 2^(e(M) - 29), M the largest magnitude): the rounds
 // in integers.  Every value is then a multiple of 2^-S with S = 52 - e(M) (149 when M is
 // subnormal), so w v 2^S is an integer below 2^84 in magnitude, held as a 2^42 + b with
 // 0 <= b < 2^42; a level keeps the sums A of the a and B of the b of its members (below
-// 2^54 for 4096 scalars) and W of their weights in three 64-bit LDS accumulators.  Its new
+// 2^56 for 16384 scalars) and W of their weights in three 64-bit LDS accumulators.  Its new
 // value is the exact integer A 2^42 + B rounded once to fp64, times 2^-S, over W in fp64,
 // rounded to fp32: the value the digit sums give, bit for bit.  When a round's levels are
 // sorted and none is a nonzero value below 2^(e(M) - 29) either, every fp64 distance is
@@ -336,7 +336,12 @@ __device__ __forceinline__ int code_from_thresholds(float x, const float* s_thr,
 // levels and thresholds; in a threshold round every scalar checks that it still lies in its
 // code's interval [t_{c-1}, t_c), and the few that left it are queued and searched by dense
 // lanes, which move their (a, b, w) between the two levels' sums (three barriers a round).
-constexpr int kCbqFastMax = 4096;                           // scalars of a codebook
+// The 16384 scalars' values, codes and queue, with a weight per entry, fill the LDS (148 KB; up to
+// 8192 scalars a weight per scalar).  By the digit path, through memory past 8192 scalars, a launch
+// with codebooks of 9792 or 10,827 scalars took 340 to 364 us (limit 4096 scalars); whole passes:
+// VGG-16 stack with k = 60 .. 1088 3.29 ms, now 3.06; ResNet-18 stack with k = 609 .. 7679 11.67, now 11.41.
+constexpr int kCbqExactMax = 16384;                         // scalars of a codebook
+constexpr int kCbqExactStep = 4096;                         // scalars whose intervals are checked at a time
 constexpr int kCbqFastLevels = 64;                          // six bits
 
 // an int128 rounded to nearest-even fp64
@@ -368,6 +373,8 @@ __device__ __forceinline__ float fp32_above(double y) {
     return __uint_as_float((u & 0x80000000u) ? u - 1u : u + 1u);
 }
 
+// WD: scalars per staged weight (1, or kDim: one weight per entry)
+template <int WD>
 __device__ void cbq_exact_rounds(const CbqParams& p, const CbqLayer& L, int m, float lo, float hi, float M, float* s_x,
                                  unsigned* s_wt, uint8_t* s_cd, unsigned short* s_q) {
     __shared__ __attribute__((aligned(16))) float s_flev[kCbqFastLevels];
@@ -385,9 +392,15 @@ __device__ void cbq_exact_rounds(const CbqParams& p, const CbqLayer& L, int m, f
     // the scalars, their weights (those <= 0 add nothing) and, later, their codes in LDS
     for (int r = tid; r < m; r += kCbqThreads) {
         s_x[r] = L.C[r];
+        if (WD > 1) continue;
         const int w = L.w ? L.w[r / kDim] : 1;
         s_wt[r] = w > 0 ? (unsigned)w : 0u;
     }
+    if (WD > 1)
+        for (int r = tid; r < m / WD; r += kCbqThreads) {
+            const int w = L.w ? L.w[r] : 1;
+            s_wt[r] = w > 0 ? (unsigned)w : 0u;
+        }
     // w v 2^S as a 2^42 + b: v 2^S from the bits (the integer mantissa shifted into place,
     // 0 <= shift <= 29 for every value that meets the condition), times w in 128 bits
     auto contrib = [&](float xv, unsigned w, long long& a, unsigned long long& b) {
@@ -401,7 +414,7 @@ __device__ void cbq_exact_rounds(const CbqParams& p, const CbqLayer& L, int m, f
     };
     // scalar r moves into level q (and, unless `first`, out of level c)
     auto move = [&](int r, int c, int q, bool first) {
-        const unsigned w = s_wt[r];
+        const unsigned w = s_wt[r / WD];
         if (!w) return;
         long long a;
         unsigned long long b;
@@ -522,26 +535,28 @@ __device__ void cbq_exact_rounds(const CbqParams& p, const CbqLayer& L, int m, f
             // code c stays while t_{c-1} <= v < t_c; the scalars that left their interval are
             // queued and searched by dense lanes (a few per round: no wave runs the search for
             // one lane)
-            // (a thread's up to four scalars: every code read first, then every bound)
-            constexpr int kPer = kCbqFastMax / kCbqThreads;
-            int c[kPer];
-            float x[kPer], tl[kPer], th[kPer];
+            // (a thread's next four scalars: every code read first, then every bound)
+            constexpr int kPer = kCbqExactStep / kCbqThreads;
+            for (int r0 = tid; r0 < m; r0 += kCbqExactStep) {
+                int c[kPer];
+                float x[kPer], tl[kPer], th[kPer];
 #pragma unroll
-            for (int u = 0; u < kPer; ++u) {
-                const int r = tid + u * kCbqThreads;
-                c[u] = r < m ? s_cd[r] : 0;
-                x[u] = r < m ? s_x[r] : 0.0f;
-            }
+                for (int u = 0; u < kPer; ++u) {
+                    const int r = r0 + u * kCbqThreads;
+                    c[u] = r < m ? s_cd[r] : 0;
+                    x[u] = r < m ? s_x[r] : 0.0f;
+                }
 #pragma unroll
-            for (int u = 0; u < kPer; ++u) {
-                tl[u] = s_thr[c[u] > 0 ? c[u] - 1 : 0];
-                th[u] = s_thr[c[u]];
-            }
+                for (int u = 0; u < kPer; ++u) {
+                    tl[u] = s_thr[c[u] > 0 ? c[u] - 1 : 0];
+                    th[u] = s_thr[c[u]];
+                }
 #pragma unroll
-            for (int u = 0; u < kPer; ++u) {
-                const int r = tid + u * kCbqThreads;
-                if (r < m && !((c[u] == 0 || tl[u] <= x[u]) && x[u] < th[u]))
-                    s_q[atomicAdd(&s_qn, 1u)] = (unsigned short)r;
+                for (int u = 0; u < kPer; ++u) {
+                    const int r = r0 + u * kCbqThreads;
+                    if (r < m && !((c[u] == 0 || tl[u] <= x[u]) && x[u] < th[u]))
+                        s_q[atomicAdd(&s_qn, 1u)] = (unsigned short)r;
+                }
             }
             __syncthreads();
             const int n = (int)s_qn;
@@ -583,7 +598,8 @@ __device__ void cbq_exact_rounds(const CbqParams& p, const CbqLayer& L, int m, f
     }
 }
 
-// Thread tid handles scalars r = tid, tid + 1024, ...  With LDS (codebooks of at most
+// Codebooks that the exact rounds do not serve: thread tid handles scalars r = tid, tid + 1024,
+// ...  With LDS (codebooks of at most
 // kCbqLdsScalars scalars) the scalars, their weights and codes are copied into LDS once;
 // otherwise every pass reads them from memory.  The level sums are kept up to date
 // incrementally: after the first full accumulation only scalars whose code changes move
@@ -603,6 +619,12 @@ __global__ __launch_bounds__(kCbqThreads) void cbq_kernel(const CbqParams p) {
     __shared__ float s_v[LDS ? kCbqLdsScalars : 1];
     __shared__ int s_wt[LDS ? kCbqLdsScalars : 1];
     __shared__ uint8_t s_code[LDS ? kCbqLdsScalars : 1];
+    // the exact rounds of codebooks past kCbqLdsScalars (weights per entry)
+    constexpr bool BIG = !LDS && FAST64;
+    __shared__ float s_bv[BIG ? kCbqExactMax : 1];
+    __shared__ unsigned s_bw[BIG ? kCbqExactMax / kDim + 1 : 1];
+    __shared__ uint8_t s_bc[BIG ? kCbqExactMax : 1];
+    __shared__ unsigned short s_bq[BIG ? kCbqExactMax : 1];
 
     const CbqLayer& L = p.L[blockIdx.x];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -654,12 +676,16 @@ __global__ __launch_bounds__(kCbqThreads) void cbq_kernel(const CbqParams p) {
         hi = fmaxf(hi, s_hi[w]);
         sm = s_sm[w] < 0.0f || sm < 0.0f ? -1.0f : fminf(sm, s_sm[w]);
     }
-    if (FAST64 && wk && m <= kCbqFastMax && sm >= 0.0f) {
+    if (FAST64 && wk && m <= (LDS ? kCbqLdsScalars : kCbqExactMax) && sm >= 0.0f) {
         const float M = fmaxf(fabsf(lo), fabsf(hi));
         if (!(sm < exact_floor(M))) {  // every value meets the exactness condition
             if constexpr (LDS) {
-                cbq_exact_rounds(p, L, m, lo, hi, M, s_v, reinterpret_cast<unsigned*>(s_wt), s_code,
-                                 reinterpret_cast<unsigned short*>(s_dig));
+                static_assert(sizeof(s_dig) >= kCbqLdsScalars * sizeof(unsigned short), "the queue of changes");
+                cbq_exact_rounds<1>(p, L, m, lo, hi, M, s_v, reinterpret_cast<unsigned*>(s_wt), s_code,
+                                    reinterpret_cast<unsigned short*>(s_dig));
+                return;
+            } else if constexpr (BIG) {
+                cbq_exact_rounds<kDim>(p, L, m, lo, hi, M, s_bv, s_bw, s_bc, s_bq);
                 return;
             }
         }

@@ -204,7 +204,7 @@ def test_update_over_several_ranges(n, k):
 
 def test_update_finish_of_many_entries():
     """Three large codebooks finished in one launch (96 entries a workgroup) and one by one (16)."""
-    sizes = [(8193, 7679), (9000, 5000), (20001, 6001)]
+    sizes = [(8193, 7679), (9000, 5000), (18001, 6001)]
     made = [layer(n, k, 80 + i) for i, (n, k) in enumerate(sizes)]
     st = kq.Stack([dev(X) for X, _ in made], [dev(C) for _, C in made])
     for i, (n, k) in enumerate(sizes):
@@ -214,3 +214,25 @@ def test_update_finish_of_many_entries():
     for i in range(3):
         assert np.array_equal(host(st.counts[i]), host(alone[i][1]))
         assert np.array_equal(host(st.C[i]).view(np.uint32), host(alone[i][0]).view(np.uint32))
+
+
+@pytest.mark.parametrize("k", [456, 910, 911, 1366, 1820, 1821])
+def test_quantize_codebook_exact_rounds_of_larger_codebooks(k):
+    """6-bit weighted k-means of 4104 to 16389 scalars, bit for bit the oracle's: around the sizes
+    held with a weight per scalar (8192) and with a weight per entry (16384), zero and huge weights,
+    few distinct values (equal levels), a value too small for the exact rounds."""
+    rng = np.random.default_rng(k)
+    laplace = rng.laplace(0, 0.03, (k, 9)).astype(np.float32)
+    laplace[np.abs(laplace) < 1e-6] = 0.0
+    w = rng.integers(0, 300, k)
+    w[::5] = 0
+    tiny = laplace.copy()
+    tiny[k // 2, 4] = np.float32(1e-12)
+    cases = [(laplace, w), (laplace, rng.integers(1, (1 << 31) - 1, k)), (tiny, w),
+             (rng.choice(np.float32([-1, 0.5, 3]), (k, 9)), rng.integers(1, 9, k))]
+    for i, (C, w) in enumerate(cases):
+        codes, levels, C_hat = kq.kq_quantize_codebook(dev(C), dev(w.astype(np.int32)), 6, kq.KQ_CBQ_WKMEANS, 30)
+        oc, ol, oh, _ = oracle.cbq_wkmeans(C, w, 6, 30)
+        assert np.array_equal(host(codes), oc), i
+        assert np.array_equal(host(levels).view(np.uint32), ol.view(np.uint32)), i
+        assert np.array_equal(host(C_hat).view(np.uint32), oh.view(np.uint32)), i
