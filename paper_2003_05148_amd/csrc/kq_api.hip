@@ -49,8 +49,12 @@ void stack_params(StackParams& p, const kq_layer* layers, int32_t l0, int32_t l1
     size_t off = 0;
     for (int32_t l = 0; l < l0; ++l) off += layer_ws_bytes(layers[l].n, layers[l].k);
     int64_t weighted_n = 0;  // update: every range of a layer reads its kernels' indices
-    for (int32_t l = l0; l < l1; ++l) weighted_n += layers[l].n * update_ranges(layers[l].k);
-    const int kpb = update_kernels_per_block(weighted_n);
+    bool ranged = false;
+    for (int32_t l = l0; l < l1; ++l) {
+        weighted_n += layers[l].n * update_ranges(layers[l].k);
+        ranged |= update_ranges(layers[l].k) > 1;
+    }
+    const int kpb = update_kernels_per_block(weighted_n, ranged);
     int unit = 0;
     for (int32_t l = l0; l < l1; ++l) {
         const kq_layer& s = layers[l];

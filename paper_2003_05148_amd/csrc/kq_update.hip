@@ -113,6 +113,7 @@ __device__ __forceinline__ void add_rows(const UpdateCtx& c, const float* __rest
 // 4096, 10 rounds 2918 and 2835 us.  The gathers of 36-byte pieces bound it.
 constexpr int kTileBatch = 4;
 constexpr int kTileKernels = kTileBatch * kUpdateThreads;
+constexpr int kValueBatch = 8;  // values in flight per thread
 __device__ __forceinline__ void add_listed(const UpdateCtx& c, const float* __restrict__ X, const int32_t* __restrict__ idx,
                                            int i0, int i1, unsigned* s_list, unsigned* s_n) {
     const int tid = threadIdx.x, lane = tid & 63;
@@ -152,17 +153,20 @@ __device__ __forceinline__ void add_listed(const UpdateCtx& c, const float* __re
         if (more) load(t0 + kTileKernels);  // in flight while this tile is added
         __syncthreads();
         const unsigned nv = s_n[par] * kDim;
-        for (unsigned v0 = (unsigned)tid; v0 < nv; v0 += kTileBatch * kUpdateThreads) {
-            float x[kTileBatch];
-            unsigned e[kTileBatch];
+        for (unsigned v0 = (unsigned)tid; v0 < nv; v0 += kValueBatch * kUpdateThreads) {
+            float x[kValueBatch];
+            unsigned e[kValueBatch];
 #pragma unroll
-            for (int u = 0; u < kTileBatch; ++u) {
-                const unsigned v = min(v0 + u * kUpdateThreads, nv - 1u), m = v / kDim, q = v - m * kDim, w = s_list[m];
-                x[u] = Xt[(w & 0xffffu) * kDim + q];
-                e[u] = (w >> 16) * kDim + q;
+            for (int u = 0; u < kValueBatch; ++u) {
+                const unsigned v = v0 + u * kUpdateThreads;
+                if (v < nv) {
+                    const unsigned m = v / kDim, q = v - m * kDim, w = s_list[m];
+                    x[u] = Xt[(w & 0xffffu) * kDim + q];
+                    e[u] = (w >> 16) * kDim + q;
+                }
             }
 #pragma unroll
-            for (int u = 0; u < kTileBatch; ++u)
+            for (int u = 0; u < kValueBatch; ++u)
                 if (v0 + u * kUpdateThreads < nv) atomicAdd(&c.s_sum[e[u]], fixed_bits(x[u], c.scale));
         }
         if (!more) break;
