@@ -1558,7 +1558,7 @@ hipError_t launch_fc_sets(const FcParams* sets, int n, hipStream_t s) {
 // coding launches, bit for bit.  When a round's levels allow no thresholds (neighbours closer than
 // 2^-50 of the largest magnitude), this and the rounds after it code every scalar by a full scan
 // of the levels, in the same launches.
-// fc6's 102,760,448 scalars, 30 rounds: 4.43 -> 1.60 ms; 4,096,000: 0.87 -> 0.48 ms.
+// fc6's 102,760,448 scalars, 30 rounds: 4.43 -> 1.60 ms; 4,096,000: 0.87 -> 0.46 ms.
 constexpr int kFsBuckets = 1024;
 constexpr int kFsSample = 4 * kFsBuckets;
 constexpr int kFsThreads = 1024;
@@ -1606,32 +1606,58 @@ __host__ __device__ inline FsView fs_view(const FcParams& p) {
     return f;
 }
 
+// The sort is bitonic with four consecutive keys per thread: partners within a thread or a wave
+// meet in registers, those further apart in one of two LDS buffers in turn (one barrier a step, 10
+// of the 78 steps; all in LDS: 37 us a launch, now 21).
 __global__ __launch_bounds__(kFsThreads) void fs_split_kernel(const FcParams p) {
-    __shared__ unsigned s_key[kFsSample];
+    constexpr int kOwn = kFsSample / kFsThreads;
+    static_assert(kOwn == 4, "a thread's keys are one uint4");
+    __shared__ uint4 s_key[2][kFsThreads];
     const FsView f = fs_view(p);
     const int tid = threadIdx.x;
-    for (int i = tid; i < kFsSample; i += kFsThreads)
-        s_key[i] = ordered_key(p.v[(long long)i * (p.m - 1) / (kFsSample - 1)]);
+    unsigned a[kOwn];
+#pragma unroll
+    for (int e = 0; e < kOwn; ++e) a[e] = ordered_key(p.v[(long long)(kOwn * tid + e) * (p.m - 1) / (kFsSample - 1)]);
     for (int e = tid; e < kFsBuckets * kDigits; e += kFsThreads) f.dig[e] = 0ull;
     f.cnt[tid] = 0u;
     f.kmin[tid] = 0xffffffffu;
     f.kmax[tid] = 0u;
     static_assert(kFsThreads == kFsBuckets, "one thread per bucket");
-    __syncthreads();
-    for (int k = 2; k <= kFsSample; k *= 2)  // bitonic, ascending
-        for (int j = k / 2; j >= 1; j /= 2) {
-            for (int e = tid; e < kFsSample / 2; e += kFsThreads) {
-                const int i = ((e & ~(j - 1)) << 1) | (e & (j - 1)), l = i | j;
-                const unsigned a = s_key[i], b = s_key[l];
-                if ((a > b) == ((i & k) == 0)) {
-                    s_key[i] = b;
-                    s_key[l] = a;
-                }
-            }
-            __syncthreads();
+    // keys i and i ^ d meet; runs of k keys ascend where i & k is clear
+    auto meet = [&](int k, int d, const unsigned (&o)[kOwn]) {
+#pragma unroll
+        for (int e = 0; e < kOwn; ++e) {
+            const int i = kOwn * tid + e;
+            a[e] = ((i & d) == 0) == ((i & k) == 0) ? min(a[e], o[e]) : max(a[e], o[e]);
         }
-    f.spl[tid] = tid == 0 ? -__builtin_inff() : key_value(s_key[tid * (kFsSample / kFsBuckets)]);
-    if (tid < 2) f.rng[tid] = key_value(s_key[tid * (kFsSample - 1)]);
+    };
+    int buf = 0;
+    for (int k = 2; k <= kFsSample; k *= 2) {
+        int d = k / 2;
+        for (; d >= kOwn * kWave; d /= 2, buf ^= 1) {
+            s_key[buf][tid] = make_uint4(a[0], a[1], a[2], a[3]);
+            __syncthreads();
+            const uint4 w = s_key[buf][tid ^ (d / kOwn)];
+            const unsigned o[kOwn] = {w.x, w.y, w.z, w.w};
+            meet(k, d, o);
+        }
+        for (; d >= kOwn; d /= 2) {
+            unsigned o[kOwn];
+#pragma unroll
+            for (int e = 0; e < kOwn; ++e) o[e] = (unsigned)__shfl_xor((int)a[e], d / kOwn);
+            meet(k, d, o);
+        }
+        if (d == 2) {
+            const unsigned o[kOwn] = {a[2], a[3], a[0], a[1]};
+            meet(k, 2, o);
+        }
+        const unsigned o[kOwn] = {a[1], a[0], a[3], a[2]};
+        meet(k, 1, o);
+    }
+    static_assert(kFsSample / kFsBuckets == kOwn, "a thread's first key is its bucket's splitter");
+    f.spl[tid] = tid == 0 ? -__builtin_inff() : key_value(a[0]);
+    if (tid == 0) f.rng[0] = key_value(a[0]);
+    if (tid == kFsThreads - 1) f.rng[1] = key_value(a[kOwn - 1]);
 }
 
 // the splitters and their index in LDS: cell c of equal-width cells over the sample's range (the
@@ -2110,7 +2136,7 @@ __global__ __launch_bounds__(kFsCutThreads) void fs_cut_kernel(const FcParams p)
 // One workgroup: the launch is a chain of memory round trips, so everything whose address is
 // known at the start is loaded in one batch (the tables that place the new thresholds among
 // them), and only the sums before a threshold's bucket wait for the bucket's number.  With a
-// load after each result, 256 threads: 8.9 us; a whole 4,096,000-scalar call 552 us, now 480.
+// load after each result, 256 threads: 8.9 us, now 6.5; a whole 4,096,000-scalar call 552 us, now 480.
 __global__ __launch_bounds__(kFsThreads) void fs_state_kernel(const FcParams p) {
     __shared__ unsigned long long s_S[kCbqMaxLevels * kFcCols];  // per level boundary, then per level
     __shared__ float s_lev[kCbqMaxLevels], s_spl[kFsBuckets];
