@@ -54,7 +54,7 @@ void stack_params(StackParams& p, const kq_layer* layers, int32_t l0, int32_t l1
         weighted_n += layers[l].n * update_ranges(layers[l].k);
         ranged |= update_ranges(layers[l].k) > 1;
     }
-    const int kpb = update_kernels_per_block(weighted_n, ranged);
+    const int kpb = update_kernels_per_block(weighted_n, ranged && l1 - l0 > 1);
     int unit = 0;
     for (int32_t l = l0; l < l1; ++l) {
         const kq_layer& s = layers[l];

@@ -32,8 +32,11 @@ constexpr int kAssignGridMax = 256;  // the persistent grid: one workgroup per C
 constexpr int kUpdateThreads = 1024;
 constexpr int kUpdateMinKernelsPerBlock = 1024;
 constexpr int kUpdateTargetBlocks = 256;
-// Where a codebook takes several ranges, two workgroups per CU: one lists members while the other
-// adds.  (The single-range ResNet-18 stack: update + finish 17.8 us with 256, 23.4 with 512.)
+// Where a codebook of a stack takes several ranges, two workgroups per CU: the layers' workgroups
+// differ in length, and one lists members while the other adds (VGG-16 stack with k = 60 .. 1088 3053
+// us a pass, 2987 with 512; ResNet-18 stack with k = 609 .. 7679 11.41 and 11.16 ms).  A single layer's
+// further partials cost more than that: 262,144 kernels, k = 1000, 20 rounds 852 us, with 512 937.
+// Single ranges: the ResNet-18 stack at k = 256, update + finish 17.8 us, with 512 23.4.
 constexpr int kUpdateRangedBlocks = 512;
 constexpr int kUpdateLdsMaxK = 768;     // LDS histogram [768][9] int64 + [768] u32
 constexpr int kFinishEntries = 16;  // codebook entries per finishing workgroup
@@ -51,8 +54,8 @@ inline int update_max_chunks(int64_t n, int32_t k) {
     return (int)(c < cap ? c : cap);
 }
 // kernels per chunk for a launch whose layers weigh `weighted_n` = sum of ranges x n
-inline int update_kernels_per_block(int64_t weighted_n, bool ranged) {
-    int64_t kpb = (weighted_n / (ranged ? kUpdateRangedBlocks : kUpdateTargetBlocks) + 255) & ~int64_t(255);
+inline int update_kernels_per_block(int64_t weighted_n, bool ranged_stack) {
+    int64_t kpb = (weighted_n / (ranged_stack ? kUpdateRangedBlocks : kUpdateTargetBlocks) + 255) & ~int64_t(255);
     if (kpb < kUpdateMinKernelsPerBlock) kpb = kUpdateMinKernelsPerBlock;
     if (kpb > (int64_t(1) << 30)) kpb = int64_t(1) << 30;
     return (int)kpb;
