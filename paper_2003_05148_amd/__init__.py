@@ -19,6 +19,7 @@ from __future__ import annotations
 import ctypes
 import math
 import os
+import threading
 
 import torch
 
@@ -206,14 +207,26 @@ class Workspace:
         return self.buf
 
 
-_workspaces: dict = {}
+# Scratch of the calls that are given no workspace: one buffer per host thread, device and stream,
+# so that calls which may overlap (two streams, two threads) never share one.  A buffer is allocated
+# and used on one stream only, so the allocator may hand its memory on as soon as it is dropped: when
+# it grows, when its thread ends, or when a thread has used _MAX_SCRATCH later ones.  Into a graph
+# goes a buffer of its own, from the graph's memory: replays may run beside any eager call.
+_MAX_SCRATCH = 8
+_scratch = threading.local()
 
 
 def _ws(device, nbytes):
-    key = device.index if device.index is not None else torch.cuda.current_device()
-    w = _workspaces.get(key)
+    if torch.cuda.is_current_stream_capturing():
+        return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
+    pool = _scratch.__dict__
+    i = device.index if device.index is not None else torch.cuda.current_device()
+    key = (i, _stream(device))
+    w = pool.get(key)
     if w is None:
-        w = _workspaces[key] = Workspace(torch.device("cuda", key))
+        if len(pool) >= _MAX_SCRATCH:
+            del pool[next(iter(pool))]  # the oldest
+        w = pool[key] = Workspace(torch.device("cuda", i))
     return w.get(nbytes)
 
 
