@@ -26,14 +26,14 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libkq.so")
 
-HOST_PATH = os.path.join(_HERE, "_kqhost.so")
+if not os.path.exists(LIB_PATH):
+    raise ImportError(f"{LIB_PATH} is not built; run __graft_entry__.build() "
+                      "(or python paper_2003_05148_amd/_build.py)")
 
-for _p in (LIB_PATH, HOST_PATH):
-    if not os.path.exists(_p):
-        raise ImportError(f"{_p} is not built; run __graft_entry__.build() "
-                          "(or python paper_2003_05148_amd/_build.py)")
-
-from . import _kqhost  # noqa: E402  (after torch: it links against its libraries)
+try:  # the descriptor arrays of large calls in C++, compiled against the installed torch
+    from . import _kqhost  # (after torch: it links against its libraries)
+except ImportError:  # absent, or built for another torch: the general path does all it does
+    _kqhost = None
 
 _P = ctypes.c_void_p
 _I32, _I64, _U32, _SZ = ctypes.c_int32, ctypes.c_int64, ctypes.c_uint32, ctypes.c_size_t
@@ -157,11 +157,15 @@ def _check(status: int, where: str):
         raise KqError(status, where)
 
 
+# a device's current stream without a Stream object around the handle, where torch has it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device) -> int:
     i = device.index
-    if i is None:
+    if i is None or _raw_stream is None:
         return torch.cuda.current_stream(device).cuda_stream
-    return torch._C._cuda_getCurrentRawStream(i)  # the same handle, without a Stream object around it
+    return _raw_stream(i)
 
 
 def _dev(t: torch.Tensor, dtype, name: str, shape=None):
@@ -777,11 +781,11 @@ def kq_reconstruct_stack(layers, workspace=None):
     needs W_ref).  Returns the list of W_hat tensors."""
     if not 1 <= len(layers) <= KQ_MAX_STACK:
         raise ValueError(f"1..{KQ_MAX_STACK} layers per call")
-    plain = _kqhost.recon_args(layers)
+    plain = _kqhost.recon_args(layers) if _kqhost is not None else None
     if plain is not None and not plain[3]:  # no squared errors: no workspace
         arr, outs, i, _ = plain
         _check(lib.kq_reconstruct_stack(arr, len(layers), _ptr(workspace), 0 if workspace is None else workspace.numel(),
-                                        torch._C._cuda_getCurrentRawStream(i)), "kq_reconstruct_stack")
+                                        _stream(torch.device("cuda", i))), "kq_reconstruct_stack")
         return outs
     arr, outs, dev = _recon_array(layers)
     nb = lib.kq_reconstruct_stack_workspace_bytes(ctypes.cast(arr, _P), len(layers))

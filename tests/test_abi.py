@@ -424,3 +424,19 @@ def test_python_stack_wrappers_check_the_distortion_slot():
             kq.kq_assign_stack(fake, dist_slot=slot)
         with pytest.raises(ValueError):
             kq.kq_update_stack(fake, dist_slot=slot)
+
+
+def test_import_without_the_host_helper():
+    """The C++ helper of the binding is an accelerator: without it the package imports and its calls
+    go through the general path (a private torch function that is missing likewise)."""
+    import subprocess
+    import sys
+    code = ("import sys, torch; sys.modules['paper_2003_05148_amd._kqhost'] = None\n"
+            "if hasattr(torch._C, '_cuda_getCurrentRawStream'): del torch._C._cuda_getCurrentRawStream\n"
+            "import paper_2003_05148_amd as kq\n"
+            "assert kq._kqhost is None\n"
+            "try: kq.kq_reconstruct_stack([{'C': torch.zeros(4, 9), 'n': 3, 'idx': torch.zeros(3, dtype=torch.int32)}])\n"
+            "except TypeError as e: assert 'C must be a CUDA' in str(e), e\n"
+            "else: raise SystemExit('CPU tensors were taken')\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
