@@ -1382,12 +1382,10 @@ __global__ __launch_bounds__(kFcSumThreads) void fc_sum_kernel(const FcStack<NS>
     __shared__ long long s_acc[kFcSumThreads / kWave][kFcCols];
     if (fc_done(p)) return;
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    long long a[kFcCols], run[kFcCols];
+    long long a[kFcCols], run = 0;
 #pragma unroll
     for (int c = 0; c < kFcCols; ++c) a[c] = 0;
-    if (tid == 0)  // the level's running sums, loaded while the partials are
-#pragma unroll
-        for (int c = 0; c < kFcCols; ++c) run[c] = p.S[q * kFcCols + c];
+    if (tid < kFcCols) run = p.S[q * kFcCols + tid];  // the level's running sums, loaded while the partials are
     if (tid < nblk && p.wg_changed[tid] != 0) {
         const long long* src = p.part + ((size_t)q * nblk + tid) * kFcCols;
 #pragma unroll
@@ -1398,20 +1396,23 @@ __global__ __launch_bounds__(kFcSumThreads) void fc_sum_kernel(const FcStack<NS>
     if (lane == 0)
         for (int c = 0; c < kFcCols; ++c) s_acc[wave][c] = a[c];
     __syncthreads();
-    if (tid == 0) {
-        unsigned long long S[kDigits];
-#pragma unroll
-        for (int c = 0; c < kFcCols; ++c) {
-            long long t = run[c];
-            for (int w = 0; w < (int)blockDim.x / kWave; ++w) t += s_acc[w][c];
-            run[c] = t;
-            if (c < kDigits) S[c] = (unsigned long long)t;
-        }
-#pragma unroll
-        for (int c = 0; c < kFcCols; ++c) p.S[q * kFcCols + c] = run[c];
-        const long long W = run[kDigits];
-        p.lev_next[q] = W > 0 ? (float)(digits_to_double(S) / (double)W) : p.lev[q];
+    if (wave != 0) return;
+    // lane c adds column c (by one thread, column after column: 2 us a launch longer)
+    if (tid < kFcCols) {
+#pragma unroll 4
+        for (int w = 0; w < (int)blockDim.x / kWave; ++w) run += s_acc[w][tid];
+        p.S[q * kFcCols + tid] = run;
     }
+    auto column = [&](int c) {
+        const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)run, c);
+        const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)((unsigned long long)run >> 32), c);
+        return (unsigned long long)hi << 32 | lo;
+    };
+    unsigned long long S[kDigits];
+#pragma unroll
+    for (int c = 0; c < kDigits; ++c) S[c] = column(c);
+    const long long W = (long long)column(kDigits);
+    if (tid == 0) p.lev_next[q] = W > 0 ? (float)(digits_to_double(S) / (double)W) : p.lev[q];
 }
 
 // run state: stop after a round without a changed code, else take the candidates
