@@ -45,6 +45,18 @@ def data(kind, m, seed):
         v = 1.0 + rng.standard_normal(m) * 0.01  # (no tiny values, so thresholds are allowed)
         v[rng.choice(m, min(m, 8), replace=False)] = rng.choice([-500.0, 500.0], min(m, 8))
         return v.astype(np.float32)
+    if kind == "pruned":                        # one value (a zero of either sign) nearly everywhere
+        v = rng.standard_normal(m).astype(np.float32)
+        v[rng.random(m) < 0.995] = 0.0
+        v[::97] *= -1.0
+        return v
+    if kind == "floor":                         # the most frequent value is the smallest
+        return np.maximum(rng.standard_normal(m), 0.5).astype(np.float32)
+    if kind == "spikes":                        # two frequent values, one of them far out, and a spread
+        v = (rng.standard_normal(m) * 0.1).astype(np.float32)
+        v[rng.random(m) < 0.4] = 0.05
+        v[rng.random(m) < 0.1] = 7.0
+        return v
     if kind == "tiny":                          # subnormal and zero values among normal ones
         v = (rng.standard_normal(m) * 1e-3).astype(np.float32)
         v[::7] = np.float32(3e-42)
@@ -155,7 +167,8 @@ def test_fc_threshold_rounds_with_a_partial_last_wave(groups):
             assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), (groups, iters, name)
 
 
-@pytest.mark.parametrize("kind", ["symmetric", "late", "integers", "constant", "two", "heavy", "outliers", "tiny"])
+@pytest.mark.parametrize("kind", ["symmetric", "late", "integers", "constant", "two", "heavy", "outliers", "tiny",
+                                  "pruned", "floor", "spikes"])
 @pytest.mark.parametrize("bits", [6, 8])
 def test_fc_partitioned_rounds(kind, bits):
     """Rounds on the set partitioned by value (thresholds asked for, v_hat given): against the
@@ -208,3 +221,32 @@ def test_fc_partitioned_rounds_of_other_widths(kind, bits):
         b = kq.kq_quantize_scalars(v, bits, iters, search="exact")
         for x, y, name in zip(a, b, ["codes", "levels", "v_hat", "rounds"]):
             assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), (kind, bits, iters, name)
+
+
+def best_us(f, reps=5):
+    f()
+    torch.cuda.synchronize()
+    best = math.inf
+    for _ in range(reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        b.synchronize()
+        best = min(best, 1e3 * a.elapsed_time(b))
+    return best
+
+
+@pytest.mark.parametrize("kind", ["pruned", "floor", "spikes"])
+def test_fc_partitioned_rounds_with_a_frequent_value(kind):
+    """A value that holds much of the set has a bucket of its own, which no round reads: the same
+    codes and levels as the exact search, and the rounds do not take longer than it (with the value's
+    neighbours in its bucket, four times as long)."""
+    v = dev(data(kind, 4 * 1024 * 1024 + 3, 5))
+    a = kq.kq_quantize_scalars(v, 6, 30)
+    b = kq.kq_quantize_scalars(v, 6, 30, search="exact")
+    for x, y, name in zip(a, b, ["codes", "levels", "v_hat", "rounds"]):
+        assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), (kind, name)
+    auto = best_us(lambda: kq.kq_quantize_scalars(v, 6, 30, *a))
+    exact = best_us(lambda: kq.kq_quantize_scalars(v, 6, 30, *b, search="exact"))
+    assert auto <= 1.5 * exact, (kind, auto, exact)
