@@ -172,9 +172,9 @@ def test_fc_threshold_rounds_with_a_partial_last_wave(groups):
 @pytest.mark.parametrize("bits", [6, 8])
 def test_fc_partitioned_rounds(kind, bits):
     """Rounds on the set partitioned by value (thresholds asked for, v_hat given): against the
-    oracle at sizes with a ragged last tile; data whose levels come closer to zero, and to each
-    other, than thresholds allow ("symmetric": from the first update; "late": after several), so
-    that the rounds go over to full scans; few distinct values (buckets of one value, empty
+    oracle at sizes with a ragged last tile; values far below the others
+    ("symmetric", "late"; the rounds that go over to full scans have tests of their own below); a
+    frequent value; few distinct values (buckets of one value, empty
     buckets); values at every scale."""
     m = 70001
     rng = np.random.default_rng(bits)
@@ -250,3 +250,64 @@ def test_fc_partitioned_rounds_with_a_frequent_value(kind):
     auto = best_us(lambda: kq.kq_quantize_scalars(v, 6, 30, *a))
     exact = best_us(lambda: kq.kq_quantize_scalars(v, 6, 30, *b, search="exact"))
     assert auto <= 1.5 * exact, (kind, auto, exact)
+
+
+def close_levels(m, bits, late=False):
+    """Half of the values near 1e-16 of the others: the two middle levels, which start the same way off
+    zero, end closer than thresholds allow (2^-50 of the largest magnitude) while the outer ones still
+    move.  From the first update on, or `late`: from the second, once they have lost the values near
+    the edge of their first range.  The set is its own mirror image (m even), so that the middle levels
+    stay the same way off zero."""
+    rng = np.random.default_rng(bits)
+    n = 1 << bits
+    m //= 2
+    v = rng.uniform(-1.0, 1.0, m) * (n - 1) / n
+    v = np.where(np.abs(v) < 4.0 / n, np.sign(v) * 4.5 / n, v)
+    tiny = rng.random(m) < 0.5
+    v[tiny] = rng.choice([-1.0, 1.0], int(tiny.sum())) * rng.uniform(5e-17, 3e-16, int(tiny.sum()))
+    if late:
+        edge = rng.random(m) < 0.1
+        v[edge] = rng.choice([-2.1, -1.9, 1.9, 2.1], int(edge.sum())) / n
+    v[0] = (n - 1) / n                          # the first levels: odd multiples of 1 / n
+    return np.concatenate([v, -v]).astype(np.float32)
+
+
+def first_close_update(v, bits, iters):
+    """The first update after which two levels are too close for thresholds, by the oracle."""
+    apart = 2.0 ** -50 * float(np.abs(v).max())
+    for it in range(1, iters + 1):
+        gap = np.diff(oracle.quantize_scalars(v, bits, it)[1].astype(np.float64))
+        if (gap[gap != 0] < apart).any():
+            return it
+    return None
+
+
+@pytest.mark.parametrize("bits", [3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("late", [False, True])
+def test_fc_full_scan_rounds_move_what_changed(bits, late):
+    """Rounds after the thresholds were given up: the first full scan forms the sums, the later ones
+    move the changes; ending with, one after and several after the first such update."""
+    v = close_levels(131072 + 78, bits, late)
+    first = first_close_update(v, bits, 4)
+    assert first == (2 if late else 1)                       # (the fallback is what runs)
+    for iters in (first, first + 1, first + 7):
+        oc, ol, ov, orr = oracle.quantize_scalars(v, bits, iters)
+        codes, levels, v_hat, rounds = kq.kq_quantize_scalars(dev(v), bits, iters, search="thresholds")
+        assert np.array_equal(host(levels).view(np.uint32), ol.view(np.uint32)), iters
+        assert np.array_equal(host(codes), oc), iters
+        assert np.array_equal(host(v_hat).view(np.uint32), ov.view(np.uint32)), iters
+        assert int(host(rounds)[0]) == orr, iters
+
+
+def test_fc_full_scan_rounds_take_no_longer_than_the_exact_search():
+    """(by a scan of all levels and whole sums in every round several times as long)"""
+    v = dev(close_levels(8_000_010, 6))
+    a = kq.kq_quantize_scalars(v, 6, 30)
+    b = kq.kq_quantize_scalars(v, 6, 30, search="exact")
+    gap = np.diff(host(a[1]).astype(np.float64))
+    assert 0 < gap[gap > 0].min() < 2.0 ** -50 and int(host(a[3])[0]) > 10   # (the fallback is what runs)
+    for x, y, name in zip(a, b, ["codes", "levels", "v_hat", "rounds"]):
+        assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), name
+    auto = best_us(lambda: kq.kq_quantize_scalars(v, 6, 30, *a), 3)
+    exact = best_us(lambda: kq.kq_quantize_scalars(v, 6, 30, *b, search="exact"), 3)
+    assert auto <= 2.0 * exact, (auto, exact)
