@@ -243,8 +243,8 @@ kq_status kq_codebook_grad_step_stack(const kq_layer* layers, int32_t n_layers, 
  *   levels are at least 2^-50 of the largest magnitude apart, so that rounding a distance to
  *   fp64 cannot reorder it, and gives the exact search's codes; KQ_F_EXACT_SEARCH /
  *   KQ_F_THRESHOLDS force one way (flags 0 = the size rule).
- *   From 3 * 2^18 scalars on (or with KQ_F_THRESHOLDS), bits >= 3, with a v_hat that does not
- *   overlap v, the set is partitioned by value into v_hat first, and a round reads only the parts
+ *   From 3 * 2^18 scalars on, with enough iters to pay for it (12, from 2^24 scalars on 5; or with
+ *   KQ_F_THRESHOLDS), bits >= 3, with a v_hat that does not overlap v, the set is partitioned by value into v_hat first, and a round reads only the parts
  *   that its level boundaries fall into; v_hat holds its documented values at the end.
  *   v device [count] fp32 (finite); codes device [count] uint8; levels device [2^bits] fp32;
  *   v_hat device [count] (= levels[codes], may be NULL); rounds device int32 (level updates

@@ -2406,12 +2406,19 @@ __global__ __launch_bounds__(kFcThreads) void fs_output_kernel(const FcParams p)
 }
 
 // whether a set takes the partitioned rounds: unweighted, with a v_hat of its own for the
-// partitioned copy, room for the tables, and large enough (or thresholds asked for).  Below, the
-// 0.13 ms of the partition cost more than the coding launches' rounds: 300,000 scalars 492 us by
-// the exact search; 1,000,000 scalars 680 us, partitioned 515.
+// partitioned copy, room for the tables, and large enough (or thresholds asked for), with rounds
+// enough to pay for the partition.  300,000 scalars take 492 us by the exact search, which the
+// partition does not reach.  What the partition costs and a round then saves, 6 bits: 786,432 scalars
+// 86 and 10 us, 1,000,003: 80 and 11, 4,096,000: 82 and 16, 20,000,000: 133 and 28, 100,000,000: 410 and
+// 103 us; at 3 bits a round of the two smaller sets saves 6.5, at 8 bits 4.5 to 6.5 us.  The rounds asked for
+// lie where both are about even over the widths: 12, 7 from 2^21 scalars on, 5 from 2^24 (1,000,003
+// scalars at one round 125 us partitioned, 54 otherwise; at 15 rounds 275 and 343).  A set that converges
+// sooner still pays: one round of 30, 20,000,000 scalars on a grid of 255 values, 435 us for 388.
 constexpr long long kFsMin = 3ll << 18;
+int fs_min_rounds(long long m) { return m < 1ll << 21 ? 12 : m < 1ll << 24 ? 7 : 5; }
 bool fs_usable(const FcParams& p) {
-    if (p.w != nullptr || p.v_hat == nullptr || p.thr_mode == 1 || (p.thr_mode == 0 && p.m < kFsMin) || p.bits < 3) return false;
+    if (p.w != nullptr || p.v_hat == nullptr || p.thr_mode == 1 || p.bits < 3) return false;
+    if (p.thr_mode == 0 && (p.m < kFsMin || p.iters < fs_min_rounds(p.m))) return false;
     const char *v = (const char*)p.v, *o = (const char*)p.v_hat;
     const long long nb = p.m * (long long)sizeof(float);
     if (v < o + nb && o < v + nb) return false;  // in place

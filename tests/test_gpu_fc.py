@@ -311,3 +311,16 @@ def test_fc_full_scan_rounds_take_no_longer_than_the_exact_search():
     auto = best_us(lambda: kq.kq_quantize_scalars(v, 6, 30, *a), 3)
     exact = best_us(lambda: kq.kq_quantize_scalars(v, 6, 30, *b, search="exact"), 3)
     assert auto <= 2.0 * exact, (auto, exact)
+
+
+@pytest.mark.parametrize("m,iters", [(1_000_003, 0), (1_000_003, 1), (1_000_003, 5), (4_096_000, 1), (4_096_000, 2)])
+def test_fc_few_rounds_do_not_pay_for_a_partition(m, iters):
+    """(partitioned, twice as long at one round)"""
+    v = dev(data("normal", m, iters))
+    a = kq.kq_quantize_scalars(v, 6, iters)
+    b = kq.kq_quantize_scalars(v, 6, iters, search="exact")
+    for x, y, name in zip(a, b, ["codes", "levels", "v_hat", "rounds"]):
+        assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), name
+    auto = best_us(lambda: kq.kq_quantize_scalars(v, 6, iters, *a))
+    exact = best_us(lambda: kq.kq_quantize_scalars(v, 6, iters, *b, search="exact"))
+    assert auto <= 1.3 * exact, (auto, exact)
