@@ -1744,8 +1744,8 @@ __device__ __forceinline__ void fs_index(const FsView& f, FsIndex& s, float lo, 
     __syncthreads();
 }
 // the buckets of B values: the splitters at or below each, by the index and then a binary search
-// within the cell (the B searches go in step); those of value hv (NaN: none) are in bucket heavy
-template <int B>
+// within the cell (the B searches go in step); HEAVY: those of value hv are in bucket heavy
+template <int B, bool HEAVY>
 __device__ __forceinline__ void fs_buckets(const FsIndex& s, const float* x, int* b, float lo, float sc, int heavy,
                                            float hv) {
     int at[B], n[B];
@@ -1753,8 +1753,9 @@ __device__ __forceinline__ void fs_buckets(const FsIndex& s, const float* x, int
 #pragma unroll
     for (int i = 0; i < B; ++i) {
         const unsigned e = s.cell[fs_cell(x[i], lo, sc)];
-        at[i] = x[i] == hv ? heavy : (int)(e & 0xffffu);
-        n[i] = x[i] == hv ? 0 : (int)(e >> 16);
+        const bool known = HEAVY && x[i] == hv;
+        at[i] = known ? heavy : (int)(e & 0xffffu);
+        n[i] = known ? 0 : (int)(e >> 16);
         any |= n[i];
     }
     while (__any(any)) {
@@ -1820,32 +1821,39 @@ __global__ __launch_bounds__(kFsThreads) void fs_hist_kernel(const FcParams p) {
     fs_index(f, s, lo, sc);
     s_n[tid] = 0u;
     __syncthreads();
-    for (long long t0 = (long long)blockIdx.x * kFsTile; t0 < p.m; t0 += (long long)gridDim.x * kFsTile) {
-        float x[kFsPer];
-        unsigned have = 0u;
-        fs_tile(p, t0, x, [&](int i, bool h) { have |= h ? 1u << i : 0u; });
+    auto tiles = [&](auto frequent) {
+        constexpr bool kHeavy = decltype(frequent)::value;
+        for (long long t0 = (long long)blockIdx.x * kFsTile; t0 < p.m; t0 += (long long)gridDim.x * kFsTile) {
+            float x[kFsPer];
+            unsigned have = 0u;
+            fs_tile(p, t0, x, [&](int i, bool h) { have |= h ? 1u << i : 0u; });
 #pragma unroll
-        for (int q = 0; q < kFsPer; q += 8) {
-            int b[8];
-            fs_buckets<8>(s, x + q, b, lo, sc, heavy, hv);
-            unsigned put = have >> q;
-            if (heavy >= 0) {
+            for (int q = 0; q < kFsPer; q += 8) {
+                int b[8];
+                fs_buckets<8, kHeavy>(s, x + q, b, lo, sc, heavy, hv);
+                unsigned put = have >> q;
+                if constexpr (kHeavy) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const bool is = (put >> i & 1u) && b[i] == heavy;
-                    nheavy += (unsigned)__popcll(__ballot(is));
-                    put &= is ? ~(1u << i) : ~0u;
+                    for (int i = 0; i < 8; ++i) {
+                        const bool is = (put >> i & 1u) && b[i] == heavy;
+                        nheavy += (unsigned)__popcll(__ballot(is));
+                        put &= is ? ~(1u << i) : ~0u;
+                    }
                 }
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (have >> (q + i) & 1u) {
+                        if (put >> i & 1u) atomicAdd(&s_n[b[i]], 1u);
+                        vlo = fminf(vlo, x[q + i]);
+                        vhi = fmaxf(vhi, x[q + i]);
+                    }
             }
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (have >> (q + i) & 1u) {
-                    if (put >> i & 1u) atomicAdd(&s_n[b[i]], 1u);
-                    vlo = fminf(vlo, x[q + i]);
-                    vhi = fmaxf(vhi, x[q + i]);
-                }
         }
-    }
+    };
+    if (heavy >= 0)  // (100,000,000 values without a frequent one: both in one loop 196 us a launch, apart 169)
+        tiles(std::true_type{});
+    else
+        tiles(std::false_type{});
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
         vlo = fminf(vlo, __shfl_xor(vlo, off));
@@ -1905,73 +1913,80 @@ __global__ __launch_bounds__(kFsThreads) void fs_scatter_kernel(const FcParams p
     const float hv = __int_as_float(f.heavy[1]);
     fs_index(f, s, lo, sc);
     float* __restrict__ out = p.v_hat;
-    for (long long t0 = (long long)blockIdx.x * kFsTile; t0 < p.m; t0 += (long long)gridDim.x * kFsTile) {
-        s_n[tid] = 0u;
-        float x[kFsPer];
-        unsigned have = 0u, br[kFsPer];  // bucket | rank << 10
-        fs_tile(p, t0, x, [&](int i, bool h) { have |= h ? 1u << i : 0u; });
-        __syncthreads();
+    auto tiles = [&](auto frequent) {
+        constexpr bool kHeavy = decltype(frequent)::value;
+        for (long long t0 = (long long)blockIdx.x * kFsTile; t0 < p.m; t0 += (long long)gridDim.x * kFsTile) {
+            s_n[tid] = 0u;
+            float x[kFsPer];
+            unsigned have = 0u, br[kFsPer];  // bucket | rank << 10
+            fs_tile(p, t0, x, [&](int i, bool h) { have |= h ? 1u << i : 0u; });
+            __syncthreads();
 #pragma unroll
-        for (int q = 0; q < kFsPer; q += 8) {
-            int b[8];
-            fs_buckets<8>(s, x + q, b, lo, sc, heavy, hv);
-            unsigned put = have >> q;
+            for (int q = 0; q < kFsPer; q += 8) {
+                int b[8];
+                fs_buckets<8, kHeavy>(s, x + q, b, lo, sc, heavy, hv);
+                unsigned put = have >> q;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) br[q + i] = (unsigned)b[i];
-            if (heavy >= 0) {  // the wave's members take consecutive ranks
-                unsigned n = 0u, r[8];
+                for (int i = 0; i < 8; ++i) br[q + i] = (unsigned)b[i];
+                if constexpr (kHeavy) {  // the wave's members take consecutive ranks
+                    unsigned n = 0u, r[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const bool is = (put >> i & 1u) && b[i] == heavy;
-                    const unsigned long long m = __ballot(is);
-                    r[i] = is ? n + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u)) : 0u;
-                    n += (unsigned)__popcll(m);
-                    put &= is ? ~(1u << i) : ~0u;
+                    for (int i = 0; i < 8; ++i) {
+                        const bool is = (put >> i & 1u) && b[i] == heavy;
+                        const unsigned long long m = __ballot(is);
+                        r[i] = is ? n + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u)) : 0u;
+                        n += (unsigned)__popcll(m);
+                        put &= is ? ~(1u << i) : ~0u;
+                    }
+                    unsigned first = 0u;
+                    if (lane == 0 && n) first = atomicAdd(&s_n[heavy], n);
+                    first = (unsigned)__builtin_amdgcn_readfirstlane((int)first);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        if (b[i] == heavy) br[q + i] |= (first + r[i]) << 10;
                 }
-                unsigned first = 0u;
-                if (lane == 0 && n) first = atomicAdd(&s_n[heavy], n);
-                first = (unsigned)__builtin_amdgcn_readfirstlane((int)first);
 #pragma unroll
                 for (int i = 0; i < 8; ++i)
-                    if (b[i] == heavy) br[q + i] |= (first + r[i]) << 10;
+                    if (put >> i & 1u) br[q + i] |= atomicAdd(&s_n[b[i]], 1u) << 10;
             }
+            __syncthreads();
+            const unsigned n = s_n[tid];
+            s_at[tid] = n ? atomicAdd(&f.cur[tid], n) : 0u;
+            unsigned inc = n;
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (put >> i & 1u) br[q + i] |= atomicAdd(&s_n[b[i]], 1u) << 10;
-        }
-        __syncthreads();
-        const unsigned n = s_n[tid];
-        s_at[tid] = n ? atomicAdd(&f.cur[tid], n) : 0u;
-        unsigned inc = n;
+            for (int off = 1; off < kWave; off <<= 1) {
+                const unsigned o = __shfl_up(inc, off);
+                if (lane >= off) inc += o;
+            }
+            if (lane == kWave - 1) s.wsum[wave] = inc;
+            __syncthreads();
+            unsigned at = inc - n;
+            for (int w = 0; w < wave; ++w) at += s.wsum[w];
+            s_first[tid] = at;
+            __syncthreads();
 #pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const unsigned o = __shfl_up(inc, off);
-            if (lane >= off) inc += o;
-        }
-        if (lane == kWave - 1) s.wsum[wave] = inc;
-        __syncthreads();
-        unsigned at = inc - n;
-        for (int w = 0; w < wave; ++w) at += s.wsum[w];
-        s_first[tid] = at;
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < kFsPer; ++q)
-            if (have >> q & 1u) s_val[s_first[br[q] & (kFsBuckets - 1)] + (br[q] >> 10)] = x[q];
-        __syncthreads();
-        // half a wave per bucket
-        constexpr int kHalves = 2 * kFsThreads / kWave;
-        const int h = 2 * wave + (lane >> 5), l = lane & 31;
+            for (int q = 0; q < kFsPer; ++q)
+                if (have >> q & 1u) s_val[s_first[br[q] & (kFsBuckets - 1)] + (br[q] >> 10)] = x[q];
+            __syncthreads();
+            // half a wave per bucket
+            constexpr int kHalves = 2 * kFsThreads / kWave;
+            const int h = 2 * wave + (lane >> 5), l = lane & 31;
 #pragma unroll 4
-        for (int b = h; b < kFsBuckets; b += kHalves) {
-            const unsigned c = b == heavy ? 0u : s_n[b], g = s_at[b], v = s_first[b];
-            for (unsigned i = l; i < c; i += 32) out[g + i] = s_val[v + i];
+            for (int b = h; b < kFsBuckets; b += kHalves) {
+                const unsigned c = kHeavy && b == heavy ? 0u : s_n[b], g = s_at[b], v = s_first[b];
+                for (unsigned i = l; i < c; i += 32) out[g + i] = s_val[v + i];
+            }
+            if constexpr (kHeavy) {
+                const unsigned c = s_n[heavy], g = s_at[heavy], v = s_first[heavy];
+                for (unsigned i = tid; i < c; i += kFsThreads) out[g + i] = s_val[v + i];
+            }
+            __syncthreads();
         }
-        if (heavy >= 0) {
-            const unsigned c = s_n[heavy], g = s_at[heavy], v = s_first[heavy];
-            for (unsigned i = tid; i < c; i += kFsThreads) out[g + i] = s_val[v + i];
-        }
-        __syncthreads();
-    }
+    };
+    if (heavy >= 0)
+        tiles(std::true_type{});
+    else
+        tiles(std::false_type{});
 }
 
 // Exact sum of values in registers: three 32-bit digits from digit d0 on, as 64-bit counts (each
