@@ -1341,36 +1341,6 @@ hipError_t launch_fc_assign(const FcStack<NS>& st, dim3 G, hipStream_t s) {
     return hipGetLastError();
 }
 
-// one workgroup per level: running exact sum += the partials; candidate level
-// v summed over the wave's 64 lanes (wrapping integer adds, any order), in every lane: the half
-// and row swaps, then DPP moves inside a row (the butterfly of the fp64 wave sum)
-__device__ __forceinline__ long long wave_sum_i64(long long v) {
-    auto add_pair = [](long long x, unsigned lo, unsigned hi) {
-        return x + (long long)(((unsigned long long)hi << 32) | lo);
-    };
-    {
-        const auto a = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
-        const auto b = __builtin_amdgcn_permlane32_swap((unsigned)(v >> 32), (unsigned)(v >> 32), false, false);
-        v = add_pair(add_pair(0, a[0], b[0]), a[1], b[1]);
-    }
-    {
-        const auto a = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
-        const auto b = __builtin_amdgcn_permlane16_swap((unsigned)(v >> 32), (unsigned)(v >> 32), false, false);
-        v = add_pair(add_pair(0, a[0], b[0]), a[1], b[1]);
-    }
-    auto dpp = [&](auto ctl) {
-        constexpr int C = decltype(ctl)::value;
-        const unsigned lo = __builtin_amdgcn_mov_dpp((unsigned)v, C, 0xF, 0xF, true);
-        const unsigned hi = __builtin_amdgcn_mov_dpp((unsigned)(v >> 32), C, 0xF, 0xF, true);
-        v = add_pair(v, lo, hi);
-    };
-    dpp(std::integral_constant<int, 0x128>{});  // row_ror:8
-    dpp(std::integral_constant<int, 0x124>{});  // row_ror:4
-    dpp(std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]
-    dpp(std::integral_constant<int, 0xB1>{});   // quad_perm [1,0,3,2]
-    return v;
-}
-
 // one workgroup per level, a thread per partial: thread b reads partial b (the partials of a level are
 // contiguous); a workgroup whose codes did not change added nothing and is skipped (every
 // first-pass partial is read)

@@ -7,6 +7,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "kq.h"
 
 namespace kq {
@@ -253,6 +255,35 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
     v = dpp_add<0x124>(v);  // row_ror:4
     v = dpp_add<0x4E>(v);   // quad_perm [2,3,0,1]
     return dpp_add<0xB1>(v);  // quad_perm [1,0,3,2]
+}
+
+// v summed over the wave's 64 lanes (wrapping integer adds, any order), in every lane: the half
+// and row swaps, then DPP moves inside a row (the butterfly of the fp64 wave sum)
+__device__ __forceinline__ long long wave_sum_i64(long long v) {
+    auto add_pair = [](long long x, unsigned lo, unsigned hi) {
+        return x + (long long)(((unsigned long long)hi << 32) | lo);
+    };
+    {
+        const auto a = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+        const auto b = __builtin_amdgcn_permlane32_swap((unsigned)(v >> 32), (unsigned)(v >> 32), false, false);
+        v = add_pair(add_pair(0, a[0], b[0]), a[1], b[1]);
+    }
+    {
+        const auto a = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+        const auto b = __builtin_amdgcn_permlane16_swap((unsigned)(v >> 32), (unsigned)(v >> 32), false, false);
+        v = add_pair(add_pair(0, a[0], b[0]), a[1], b[1]);
+    }
+    auto dpp = [&](auto ctl) {
+        constexpr int C = decltype(ctl)::value;
+        const unsigned lo = __builtin_amdgcn_mov_dpp((unsigned)v, C, 0xF, 0xF, true);
+        const unsigned hi = __builtin_amdgcn_mov_dpp((unsigned)(v >> 32), C, 0xF, 0xF, true);
+        v = add_pair(v, lo, hi);
+    };
+    dpp(std::integral_constant<int, 0x128>{});  // row_ror:8
+    dpp(std::integral_constant<int, 0x124>{});  // row_ror:4
+    dpp(std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]
+    dpp(std::integral_constant<int, 0xB1>{});   // quad_perm [1,0,3,2]
+    return v;
 }
 
 // Sum of m fp64 values in a fixed order by a workgroup of NT threads (a multiple of 64):

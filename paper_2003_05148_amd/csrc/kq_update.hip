@@ -53,6 +53,12 @@ __device__ __forceinline__ float sqdist9u(const float* x, const float* __restric
     return acc;
 }
 
+// the nine values of a row
+__device__ __forceinline__ void mem_row_of(float (&x)[kDim], const float* __restrict__ r) {
+#pragma unroll
+    for (int d = 0; d < kDim; ++d) x[d] = r[d];
+}
+
 struct UpdateCtx {
     unsigned long long* s_sum;  // [krange][9]
     unsigned* s_cnt;            // [krange]
@@ -359,15 +365,22 @@ __global__ __launch_bounds__(kFinishThreads) void update_finish_kernel(const Sta
 // per thread: the list is dense) to LDS sums and finishes its entries.  Every workgroup reads the
 // indices again (k / 16 times 4 n bytes: 1.2 MB at n = 4096, k = 1228), which costs less than the
 // partials and the second launch of the general path: 4096 kernels, k = 700: 5.1 + 3.8 us and the
-// gap between them, now 4.3 us.  The last nlayers workgroups add the distortion partials.
+// gap between them, now 4.3 us.  An entry with most of the kernels (a pruned layer's zeros) leaves its
+// workgroup alone with them: the list is built by ballots, and from kHeavyMembers members on a sample of
+// it tells the most frequent entry, whose rows are then added in registers, a row per thread.  A fit of
+// 16384 kernels, 20 rounds, none, half and 90 % of them zero: k = 256 with LDS atomics per member and
+// value 308, 652 and 942 us, now 305, 432 and 459 (member sums fused into the assignment 350 us all
+// three); k = 1000 335, 683 and 988, now 333, 475 and 498 (update and finish 402).  The last nlayers
+// workgroups add the distortion partials.
 constexpr int kSmallThreads = 1024;
-__global__ __launch_bounds__(kSmallThreads) void update_small_kernel(const StackParams p) {
+constexpr int kHeavyMembers = 3072;
+__global__ __launch_bounds__(kSmallThreads, 8) void update_small_kernel(const StackParams p) {
     __shared__ unsigned s_list[kUpdateSmallN];  // kernel | entry of the workgroup << 16
     __shared__ unsigned long long s_sum[kFinishEntries * kDim];
     __shared__ unsigned s_cnt[kFinishEntries];
     __shared__ unsigned s_n, s_mx;
     __shared__ double s_w[kSumThreads / kWave];
-    const int b = blockIdx.x, tid = threadIdx.x;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1);
     if (b >= p.total_units) {  // the distortion of layer b - total
         const DevLayer& L = p.L[b - p.total_units];
         if (L.dist == nullptr) return;
@@ -400,29 +413,94 @@ __global__ __launch_bounds__(kSmallThreads) void update_small_kernel(const Stack
     if (tid < kFinishEntries) s_cnt[tid] = 0u;
     if (tid == 0) s_n = 0u;
     __syncthreads();
-    for (int i0 = tid; i0 < n; i0 += kBatch * kSmallThreads) {
-        if (i0 != tid) {
+    for (int i0 = 0; i0 < n; i0 += kBatch * kSmallThreads) {  // (uniform)
+        if (i0 != 0) {
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) jb[u] = i0 + u * kSmallThreads < n ? idx[i0 + u * kSmallThreads] : -1;
+            for (int u = 0; u < kBatch; ++u) {
+                const int i = i0 + u * kSmallThreads + tid;
+                jb[u] = i < n ? idx[i] : -1;
+            }
         }
+        unsigned before[kBatch], found = 0u;
+        bool in[kBatch];
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
-            const unsigned jr = (unsigned)(jb[u] - j0);
-            if (jr < (unsigned)kFinishEntries && jb[u] < k) {  // (indices outside [0, k) are ignored)
-                atomicAdd(&s_cnt[jr], 1u);
-                if (sums) s_list[atomicAdd(&s_n, 1u)] = (unsigned)(i0 + u * kSmallThreads) | jr << 16;
+            in[u] = (unsigned)(jb[u] - j0) < (unsigned)kFinishEntries && jb[u] < k;  // (others are ignored)
+            const unsigned long long m = __ballot(in[u]);
+            before[u] = found + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+            found += (unsigned)__popcll(m);
+        }
+        unsigned at = 0u;
+        if (lane == 0 && found) at = atomicAdd(&s_n, found);
+        at = (unsigned)__builtin_amdgcn_readfirstlane((int)at);
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            if (in[u]) s_list[at + before[u]] = (unsigned)(i0 + u * kSmallThreads + tid) | (unsigned)(jb[u] - j0) << 16;
+    }
+    __syncthreads();
+    const int total = (int)s_n;
+    const double scale = fixed_scale(shift);
+    int heavy = -1;  // an entry with at least a quarter of many members
+    if (total >= kHeavyMembers) {
+        const unsigned own = s_list[(unsigned)lane * (unsigned)total / kWave] >> 16;
+        int most = kWave / 4 - 1;
+#pragma unroll
+        for (int q = 0; q < kFinishEntries; ++q) {
+            const int c = __popcll(__ballot(own == (unsigned)q));
+            heavy = c > most ? q : heavy;
+            most = c > most ? c : most;
+        }
+    }
+    if (heavy < 0) {
+        for (int m = tid; m < total; m += kSmallThreads) atomicAdd(&s_cnt[s_list[m] >> 16], 1u);
+        if (sums)
+            for (unsigned v = tid; v < (unsigned)total * kDim; v += kSmallThreads) {
+                const unsigned m = v / kDim, q = v - m * kDim, w = s_list[m];
+                atomicAdd(&s_sum[(w >> 16) * kDim + q], fixed_bits(X[(size_t)(w & 0xffffu) * kDim + q], scale));
             }
+    } else {
+        long long acc[kDim];
+        unsigned z = 0u;
+#pragma unroll
+        for (int q = 0; q < kDim; ++q) acc[q] = 0;
+        constexpr int kRows = 2;  // rows in flight per thread
+        for (int m0 = tid; m0 < total; m0 += kRows * kSmallThreads) {
+            unsigned w[kRows];
+            float x[kRows][kDim];
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                const int m = m0 + u * kSmallThreads;
+                w[u] = s_list[m < total ? m : m0];
+                if (sums) mem_row_of(x[u], X + (size_t)(w[u] & 0xffffu) * kDim);
+            }
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                if (m0 + u * kSmallThreads >= total) continue;
+                const unsigned jr = w[u] >> 16;
+                if ((int)jr == heavy) {
+                    ++z;
+                    if (sums)
+#pragma unroll
+                        for (int q = 0; q < kDim; ++q) acc[q] += (long long)fixed_bits(x[u][q], scale);
+                } else {
+                    atomicAdd(&s_cnt[jr], 1u);
+                    if (sums)
+#pragma unroll
+                        for (int q = 0; q < kDim; ++q) atomicAdd(&s_sum[jr * kDim + q], fixed_bits(x[u][q], scale));
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kDim; ++q) acc[q] = wave_sum_i64(acc[q]);
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) z += (unsigned)__shfl_xor((int)z, off);
+        if (lane == 0) {
+            atomicAdd(&s_cnt[heavy], z);
+#pragma unroll
+            for (int q = 0; q < kDim; ++q) atomicAdd(&s_sum[heavy * kDim + q], (unsigned long long)acc[q]);
         }
     }
     __syncthreads();
-    if (sums) {
-        const double scale = fixed_scale(shift);
-        for (unsigned v = tid; v < s_n * kDim; v += kSmallThreads) {
-            const unsigned m = v / kDim, q = v - m * kDim, w = s_list[m];
-            atomicAdd(&s_sum[(w >> 16) * kDim + q], fixed_bits(X[(size_t)(w & 0xffffu) * kDim + q], scale));
-        }
-        __syncthreads();
-    }
     if (!mine) return;
     const unsigned z = s_cnt[e];
     if (d == 9) {

@@ -174,6 +174,55 @@ def test_update_of_small_layers(shape):
             assert np.array_equal(host(gz), np.bincount(host(a), minlength=C.shape[0]))
 
 
+# members of one workgroup's entries at the edge where a frequent entry is added in registers (3072)
+@pytest.mark.parametrize("n,k,share", [(3071, 200, 1.0), (3072, 200, 1.0), (3073, 200, 1.0), (16384, 300, 0.99), (16384, 300, 0.4),
+                                       (16384, 300, 0.2), (12289, 4096, 0.9), (16000, 130, 0.7), (16384, 1024, 1.0)])
+def test_update_of_small_layers_with_a_frequent_entry(n, k, share):
+    """The one-launch update against the general one, bit for bit, with indices of which one entry has
+    a large share, at both ends of its workgroup's entries and with another frequent one beside it."""
+    X, C = layer(n, k, n + k)
+    st = kq.Stack([dev(X)], [dev(C)], iters=2)
+    rng = np.random.default_rng(k)
+    for entry in (0, 15 if k > 15 else k - 1, k - 1):
+        idx = rng.integers(0, k, n).astype(np.int32)
+        frequent = rng.random(n) < share
+        idx[frequent] = entry
+        idx[frequent & (rng.random(n) < 0.2)] = max(entry - 1, 0)
+        kq.kq_assign_stack(st)
+        st.idx[0].copy_(dev(idx))
+        st.set_codebooks([dev(C)])
+        Cn, z, _ = kq.kq_update(st.X[0], st.idx[0], dev(C))
+        for counts_only in (False, True):
+            kq.kq_update_stack(st, distortion_from_assign=True, counts_only=counts_only)
+            assert np.array_equal(host(st.counts[0]), np.bincount(idx, minlength=k)) and torch.equal(st.counts[0], z)
+            assert np.array_equal(host(st.C[0]).view(np.uint32), host(Cn).view(np.uint32)), entry
+
+
+def best_us(f, reps=5):
+    f()
+    torch.cuda.synchronize()
+    best = np.inf
+    for _ in range(reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        b.synchronize()
+        best = min(best, 1e3 * a.elapsed_time(b))
+    return best
+
+
+def test_fit_of_a_small_layer_with_many_zero_kernels():
+    """(with an atomic per member and value: three times as long as without zeros)"""
+    X, C = layer(16384, 256, 7)
+    Z = X.copy()
+    Z[np.random.default_rng(1).random(16384) < 0.9] = 0
+    C[0] = 0
+    X, Z, C = dev(X), dev(Z), dev(C)
+    plain, zeros = best_us(lambda: kq.kq_fit_layer(X, C, 20)), best_us(lambda: kq.kq_fit_layer(Z, C, 20))
+    assert zeros <= 2.2 * plain, (zeros, plain)
+
+
 # runs of few units: one to six per workgroup, several waves per unit, and k at the edges
 @pytest.mark.parametrize("n,k", [(64, 300), (100, 257), (4096, 600), (64 * 256 * 2, 700), (64 * 256 * 3 + 5, 1024),
                                  (64 * 256 * 7, 300), (1, 1024)])
