@@ -214,7 +214,7 @@ kq_status run_update(const kq_layer* layers, int32_t l0, int32_t l1, unsigned ch
     stack_params(p, layers, l0, l1, ws, Op::Update, slot, C_old, kflags, from_assign || sums_from_assign);
     p.derive_shift = derive ? 1 : 0;
     bool small = from_assign && !sums_from_assign && (kflags & kFlagGrad) == 0;
-    for (int32_t l = l0; l < l1; ++l) small &= layers[l].n <= kUpdateSmallN && layers[l].k <= kUpdateSmallK;
+    for (int32_t l = l0; l < l1; ++l) small &= update_small_fits(layers[l].n, layers[l].k);
     if (small) return hip_status(launch_update_small(p, s));
     if (sums_from_assign) {
         int wf[KQ_MAX_STACK], ns[KQ_MAX_STACK];

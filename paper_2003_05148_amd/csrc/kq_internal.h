@@ -42,9 +42,18 @@ constexpr int kUpdateTargetBlocks = 256;
 constexpr int kUpdateRangedBlocks = 512;
 constexpr int kUpdateLdsMaxK = 768;     // LDS histogram [768][9] int64 + [768] u32
 constexpr int kFinishEntries = 16;  // codebook entries per finishing workgroup
-// updates whose layers all have at most this many kernels (and k <= kUpdateSmallK) take one launch
+// Updates whose layers all have at most kUpdateSmallN kernels (and k <= kUpdateSmallK) take one launch,
+// in which a workgroup adds all members of its kFinishEntries entries: about kUpdateSmallMembers of them
+// at most.  20 rounds of a layer of 4096 kernels, k = 300, beside another one, two launches a round and
+// one: 16384 kernels, k = 16 (16384 members) 340 and 762 us; k = 60 (4369) 344 and 405; k = 128 (2048)
+// 345 and 337; 4096 kernels, k = 16 (4096) 335 and 358; 2048, k = 16 (2048) 337 and 290.
 constexpr int kUpdateSmallN = 16384;
 constexpr int kUpdateSmallK = 4096;
+constexpr int kUpdateSmallMembers = 2048;
+inline bool update_small_fits(int64_t n, int32_t k) {
+    const int64_t entries = k < kFinishEntries ? k : kFinishEntries;
+    return n <= kUpdateSmallN && k <= kUpdateSmallK && n * entries <= (int64_t)kUpdateSmallMembers * k;
+}
 constexpr size_t kUpdatePartialBudget = size_t(1) << 24;  // bytes of partials per layer above 768 entries
 
 inline int update_ranges(int32_t k) { return (k + kUpdateLdsMaxK - 1) / kUpdateLdsMaxK; }

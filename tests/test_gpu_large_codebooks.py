@@ -141,8 +141,9 @@ def test_wide_codebooks_share_their_launches(bits):
             assert torch.equal(x.view(torch.uint8), z.view(torch.uint8))
 
 
-# one launch updates layers of at most 16384 kernels and 4096 entries; above, the general path
-SMALL_UPDATES = [[(1, 1)], [(16384, 300)], [(16385, 300)], [(16384, 4096)], [(4096, 4097)], [(8191, 1000), (100, 17), (700, 513)]]
+# one launch updates layers of at most 16384 kernels and 4096 entries, with about 2048 kernels to 16
+# entries at most; beyond, the general path
+SMALL_UPDATES = [[(2048, 16)], [(2049, 16)], [(2048, 1)], [(16384, 128)], [(16384, 127)], [(1, 1)], [(16384, 300)], [(16385, 300)], [(16384, 4096)], [(4096, 4097)], [(8191, 1000), (100, 17), (700, 513)]]
 
 
 @pytest.mark.parametrize("shape", SMALL_UPDATES)
@@ -221,6 +222,25 @@ def test_fit_of_a_small_layer_with_many_zero_kernels():
     X, Z, C = dev(X), dev(Z), dev(C)
     plain, zeros = best_us(lambda: kq.kq_fit_layer(X, C, 20)), best_us(lambda: kq.kq_fit_layer(Z, C, 20))
     assert zeros <= 2.2 * plain, (zeros, plain)
+
+
+def test_fits_of_mixed_small_layers():
+    """A layer with many kernels and few entries beside one that takes the one-launch update: as long as
+    both alone at most (the first in that launch too: half as long again as both)."""
+    made = [layer(16384, 16, 1), layer(4096, 300, 2)]
+    st = kq.Stack([dev(X) for X, _ in made], [dev(C) for _, C in made], iters=20)
+
+    def both():
+        st.set_codebooks(start)
+        kq.kq_fit_stack(st, 20)
+
+    start = [c.clone() for c in st.C]
+    alone = [best_us(lambda i=i: kq.kq_fit_layer(st.X[i], start[i], 20)) for i in range(2)]
+    together = best_us(both)
+    assert together <= sum(alone), (together, alone)
+    for i in range(2):
+        C, idx, z, _ = kq.kq_fit_layer(st.X[i], start[i], 20)
+        assert torch.equal(C, st.C[i]) and torch.equal(idx, st.idx[i]) and torch.equal(z, st.counts[i])
 
 
 # runs of few units: one to six per workgroup, several waves per unit, and k at the edges
