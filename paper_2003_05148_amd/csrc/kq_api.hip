@@ -39,6 +39,39 @@ kq_status check_ws(void* ws, size_t ws_bytes, size_t need) {
 
 enum class Op { Assign, Update };
 
+// Kernels per chunk of an update launch over layers [l0, l1).  Every range of a layer reads its
+// kernels' indices, so a launch weighs the sum of ranges x n.  Where a codebook takes several ranges, a
+// layer's last chunk and its ranges leave that estimate with more workgroups than asked for, and the
+// few that come second take as long as the first: the chunks then grow until the workgroups fit.
+int update_kernels(const kq_layer* layers, int32_t l0, int32_t l1) {
+    int64_t weighted = 0;
+    bool ranged = false;
+    for (int32_t l = l0; l < l1; ++l) {
+        weighted += layers[l].n * update_ranges(layers[l].k);
+        ranged |= update_ranges(layers[l].k) > 1;
+    }
+    if (!ranged) return update_kernels_per_block(weighted, kUpdateTargetBlocks);
+    auto count = [&](int kpb) {
+        int64_t c = 0;
+        for (int32_t l = l0; l < l1; ++l) {
+            const int chunk = update_chunk(layers[l].n, layers[l].k, kpb);
+            c += update_ranges(layers[l].k) * ((layers[l].n + chunk - 1) / chunk);
+        }
+        return c;
+    };
+    auto fit = [&](int target) {
+        const int least = update_kernels_per_block(weighted, target);
+        for (int kpb = least; kpb <= 2 * (int64_t)least; kpb += kpb / 16 & ~255 ? kpb / 16 & ~255 : 256)
+            if (count(kpb) <= target) return kpb;
+        return least;
+    };
+    if (weighted >= kUpdateLongMin) {
+        const int kpb = fit(kUpdateLongBlocks);
+        if (count(kpb) >= kUpdateLongBlocks * 7 / 8) return kpb;
+    }
+    return fit(kUpdateTargetBlocks);
+}
+
 // Launch parameters for layers [l0, l1) of a stack.  `base` points at the workspace
 // of layer 0 (the regions of the layers follow each other in order).  C_alt (nullable):
 // for an assignment the codebook of each layer to assign against instead of its C; for an
@@ -48,13 +81,7 @@ void stack_params(StackParams& p, const kq_layer* layers, int32_t l0, int32_t l1
     memset(&p, 0, sizeof(p));
     size_t off = 0;
     for (int32_t l = 0; l < l0; ++l) off += layer_ws_bytes(layers[l].n, layers[l].k);
-    int64_t weighted_n = 0;  // update: every range of a layer reads its kernels' indices
-    bool ranged = false;
-    for (int32_t l = l0; l < l1; ++l) {
-        weighted_n += layers[l].n * update_ranges(layers[l].k);
-        ranged |= update_ranges(layers[l].k) > 1;
-    }
-    const int kpb = update_kernels_per_block(weighted_n, ranged && l1 - l0 > 1);
+    const int kpb = op == Op::Update ? update_kernels(layers, l0, l1) : 0;
     int unit = 0;
     for (int32_t l = l0; l < l1; ++l) {
         const kq_layer& s = layers[l];

@@ -34,12 +34,15 @@ constexpr int kAssignGridMax = 256;  // the persistent grid: one workgroup per C
 constexpr int kUpdateThreads = 1024;
 constexpr int kUpdateMinKernelsPerBlock = 1024;
 constexpr int kUpdateTargetBlocks = 256;
-// Where a codebook of a stack takes several ranges, two workgroups per CU: the layers' workgroups
-// differ in length, and one lists members while the other adds (VGG-16 stack with k = 60 .. 1088 3053
-// us a pass, 2987 with 512; ResNet-18 stack with k = 609 .. 7679 11.41 and 11.16 ms).  A single layer's
-// further partials cost more than that: 262,144 kernels, k = 1000, 20 rounds 852 us, with 512 937.
-// Single ranges: the ResNet-18 stack at k = 256, update + finish 17.8 us, with 512 23.4.
-constexpr int kUpdateRangedBlocks = 512;
+// Two workgroups per CU (one lists members while the other adds) where the chunks of a launch over
+// several ranges are long enough to pay for twice the partials, about 3 us: from kUpdateLongMin
+// weighed kernels on, unless the partials' bound leaves too few workgroups.  Update and finish with 256
+// and 512 workgroups: the ResNet-18 stack with k = 609 .. 7679 (8.7M) 59.8 and 52.9 us; two layers of
+// 262,144 kernels, k = 7000 (5.2M) 36.4 and 36.5; k = 1000 (1.0M) 24.1 and 27.8; the VGG-16 stack with
+// k = 60 .. 1088 (1.8M) 35.8 and 37.5; 1,048,576 kernels, k = 4096 (6.3M, 306 of 512) 47.6 and 50.5.
+// Single ranges: the ResNet-18 stack at k = 256 17.8 and 23.4.
+constexpr int kUpdateLongBlocks = 512;
+constexpr int64_t kUpdateLongMin = 7000000;
 constexpr int kUpdateLdsMaxK = 768;     // LDS histogram [768][9] int64 + [768] u32
 constexpr int kFinishEntries = 16;  // codebook entries per finishing workgroup
 // Updates whose layers all have at most kUpdateSmallN kernels (and k <= kUpdateSmallK) take one launch,
@@ -64,9 +67,10 @@ inline int update_max_chunks(int64_t n, int32_t k) {
     if (cap < 1) cap = 1;
     return (int)(c < cap ? c : cap);
 }
-// kernels per chunk for a launch whose layers weigh `weighted_n` = sum of ranges x n
-inline int update_kernels_per_block(int64_t weighted_n, bool ranged_stack) {
-    int64_t kpb = (weighted_n / (ranged_stack ? kUpdateRangedBlocks : kUpdateTargetBlocks) + 255) & ~int64_t(255);
+// kernels per chunk for a launch of about `target` workgroups whose layers weigh `weighted_n` = sum of
+// ranges x n
+inline int update_kernels_per_block(int64_t weighted_n, int target) {
+    int64_t kpb = (weighted_n / target + 255) & ~int64_t(255);
     if (kpb < kUpdateMinKernelsPerBlock) kpb = kUpdateMinKernelsPerBlock;
     if (kpb > (int64_t(1) << 30)) kpb = int64_t(1) << 30;
     return (int)kpb;

@@ -117,7 +117,7 @@ __device__ __forceinline__ void add_rows(const UpdateCtx& c, const float* __rest
 // Whole passes, a row per thread and step before: the VGG-16 stack with k = 60 .. 1088 3452 us,
 // listed 3309; the ResNet-18 stack with k = 609 .. 7679 12.61 and 12.20 ms; 1,048,576 kernels, k =
 // 4096, 10 rounds 2918 and 2835 us.  Two barriers a tile and the gathers of 36-byte pieces bound it
-// (a launch on these stacks 24 and 53 us before, 16 and 34 with kUpdateRangedBlocks).
+// (a launch on these stacks 24 and 53 us before, 16 and 34 with two workgroups per CU).
 constexpr int kTileBatch = 4;
 constexpr int kTileKernels = kTileBatch * kUpdateThreads;
 constexpr int kValueBatch = 8;  // values in flight per thread
