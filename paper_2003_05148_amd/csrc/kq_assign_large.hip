@@ -11,10 +11,12 @@
 // K = 32, 112 ns with K = 16.
 //
 // Screening.  Scaled by powers of two, ys = x 2^b and cs = c 2^a with max |c_jd| 2^a in [2^12,
-// 2^13) over the codebook and b = a, or less where max |x_d| exceeds max |c_jd| (then |ys_d| <
-// 2^13 too), the score s_j = |c_j|^2 - 2 x . c_j becomes, times 2^(a+b),
+// 2^13) over the codebook but its far entries (kFarExp; they are scored as padding) and b = a, or less
+// where max |x_d| exceeds max |c_jd| (then |ys_d| < 2^13 too), the score s_j = |c_j|^2 - 2 x . c_j
+// becomes, times 2^(a+b),
 //     sum_{d < 9} w_jd ys_d + n_j u,   w_j = -2 cs_j,  n_j = |cs_j|^2 2^-14,  u = 2^(14 + b - a).
-// w and ys are rounded to fp16, n_j is split into three fp16 parts: 12 of the 16 terms of one
+// w and ys are rounded to fp16, n_j u is split into three products n_h u + n_m 2^-11 u + n_l 2^-22 u of
+// fp16 values (n_h = fp16(n_j), n_m = fp16(2^11 (n_j - n_h)), and so on): 12 of the 16 terms of one
 // v_mfma_f32_32x32x16_f16 per 32 x 32 tile of (entries, kernels), products exact, sums in fp32.
 // In the D layout a lane holds one kernel (column) and 16 of its 32 rows.  A segment is
 // 256 or 512 entries (8 or 16 tiles); a group is the 8 or 16 entries of one row ("slot") of it.  Each lane keeps
@@ -26,7 +28,8 @@
 // B = 2^-14 2^-b (the smallest normal fp16 in units of c and of x: a value below it may be lost
 // whole).  In units of s_j a screened score is off by at most
 //     (2^-10 + 2^-22) 2 |x| |c_j|  (both roundings to fp16, 2^-11 each)
-//   + 1.01 (6 B |c_j| + 3 A |x|) + 2^(1 - 2a)  (fp16 values that may be flushed)
+//   + 1.01 (6 B |c_j| + 3 A |x|) + 2^(-22 - 2a)  (fp16 values that may be flushed: the last below 2^-14
+//     in n_l; where b is so far below a that a u flushes, |c_j|^2 is below 2^-29 |x|^2)
 //   + 104 u0 P_j  (33: the sums of 13 terms, truncated or rounded; 9: the fp32 norm; 62: the slot
 //     number in the 5 lowest mantissa bits of a slot minimum).
 // The first group is rescored in the plain fp32 form; d* is its smallest distance, at the lowest
@@ -36,8 +39,9 @@
 // with r for |c_j|, and its fp32 distance exceeds d* once M2 + |x|^2 - d* is larger than the bound
 // plus 18 u0 (|x| + r)^2 (the fp32 |x|^2, the distance's rounding and the guard's own).  The guard
 // asks for more than
-//     theta = 1.05 (2^-9 |x| r' + 2^-17 (|x| + r')^2 + 6 B r' + 3 A |x| + 2^(1 - 2a)) + 2^-100,
-// r' = |x| + 1.01 sqrt(d*) + 2^-60.  Where it fails (1 to 7 % of the kernels), the second group is
+//     theta = 1.05 (2^-9 |x| r' + 2^-17 (|x| + r')^2 + 6 B r' + 3 A |x| + 2^(-21 - 2a)) + 2^-100,
+// r' = |x| + 1.01 sqrt(d*) + 2^-60, and for r' below the length of every far entry (an entry that is not
+// finite never wins).  Where it fails (1 to 7 % of the kernels), the second group is
 // rescored too, d* is the smaller distance of both, and the guard is asked of M3, the smallest
 // minimum of all groups but these two.  Where that fails too (about one kernel in a thousand),
 // and wherever (|x| + r')^2 >= 1e37 or a value is not finite, the kernel is rescored over the
@@ -62,6 +66,11 @@ constexpr int kResidentMaxK = kLargeLds / kOperandLds / 64 * 64;        // 4864
 constexpr int kRowsMaxK = kLargeLds / kEntryLds / 64 * 64;              // 1920
 constexpr int kStreamChunk = kLargeLds / kOperandLds / kSegMax * kSegMax;  // 4608
 constexpr int kShortSegK = 2048;  // segments of 256 entries for launches up to this codebook size
+// entries more than 2^kFarExp above the middle of the waves' largest exponents are far: they keep the
+// scale from the others, and no kernel nearer to zero than they are takes them
+constexpr int kFarExp = 12;
+// scaled: |cs_jd| < 2^13 gives |cs_j|^2 < 6.04e8; below kNearNorm an entry's operands are finite fp16 values
+constexpr float kNearNorm = 7e8f, kFarLength = 26457.0f;  // kFarLength^2 < kNearNorm
 constexpr int kStreamUnits = 8;  // units whose summaries a wave keeps while a codebook streams
 
 __device__ __forceinline__ float max2(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, __builtin_inff()); }
@@ -83,35 +92,41 @@ __device__ __forceinline__ unsigned pack16(float a, float b) {  // (a, b) rounde
 __device__ __forceinline__ float scale_of(int E) { return __uint_as_float((unsigned)(266 - E) << 23); }
 __device__ __forceinline__ float inverse_of(int E) { return __uint_as_float((unsigned)(E - 12) << 23); }
 
+// a value of at least the smallest normal fp16 in magnitude, rounded to fp16; a smaller one is zero
+__device__ __forceinline__ float half_of(float v) { return fabsf(v) < 0x1p-14f ? 0.0f : (float)(_Float16)v; }
+
 // entries [c0, c0 + cn) into LDS: fp16 operands [w_0 .. w_8, n_h, n_m, n_l, 0 ..] at s_a, in the
-// A layout [tile][lane][8 x fp16], and (ROWS) the fp32 rows at s_c; entries past the codebook are
-// padding, with a score above any trusted one
+// A layout [tile][lane][8 x fp16], and (ROWS) the fp32 rows at s_c; entries past the codebook and far
+// ones are padding, with a score above any trusted one
 template <bool ROWS>
 __device__ __forceinline__ void stage16(const float* __restrict__ C, int k, int c0, int cn, float sc, u32x4* s_a,
                                         f32x4* s_c, int tid, const float* own = nullptr) {
     for (int jl = tid; jl < cn; jl += kAssignWaves * kWave) {
         const int j = c0 + jl;
-        float c[kDim], w[kDim], n0, n1, n2;
+        float c[kDim], w[kDim], n0, n1, n2, nn = __builtin_inff();
         if (j < k) {
 #pragma unroll
             for (int d = 0; d < kDim; ++d) c[d] = (own && jl == tid) ? own[d] : C[(size_t)j * kDim + d];
-            float nn = 0.0f;
+            nn = 0.0f;
 #pragma unroll
             for (int d = 0; d < kDim; ++d) {
                 const float s = c[d] * sc;
                 nn = __fmaf_rn(s, s, nn);
                 w[d] = -2.0f * s;
             }
-            nn *= 0x1p-14f;
-            n0 = nn;
-            n1 = n0 - (float)(_Float16)n0;  // exact
-            n2 = n1 - (float)(_Float16)n1;
         } else {
 #pragma unroll
-            for (int d = 0; d < kDim; ++d) {
-                c[d] = __builtin_inff();
-                w[d] = 0.0f;
-            }
+            for (int d = 0; d < kDim; ++d) c[d] = __builtin_inff();
+        }
+        if (nn < kNearNorm) {  // (not a NaN's)
+            nn *= 0x1p-14f;
+            n0 = half_of(nn);
+            const float t1 = (nn - n0) * 0x1p11f;  // exact
+            n1 = half_of(t1);
+            n2 = half_of((t1 - n1) * 0x1p11f);
+        } else {
+#pragma unroll
+            for (int d = 0; d < kDim; ++d) w[d] = 0.0f;
             n0 = n1 = n2 = 65504.0f;
         }
         const u32x4 lo = {pack16(w[0], w[1]), pack16(w[2], w[3]), pack16(w[4], w[5]), pack16(w[6], w[7])};
@@ -133,7 +148,7 @@ __device__ __forceinline__ void stage16(const float* __restrict__ C, int k, int 
 __device__ __forceinline__ void make_b16(u32x4 (&bop)[2], const float (&x)[kDim], float sx, float u) {
     const unsigned D[4] = {pack16(x[0] * sx, x[1] * sx), pack16(x[2] * sx, x[3] * sx), pack16(x[4] * sx, x[5] * sx),
                            pack16(x[6] * sx, x[7] * sx)};
-    const unsigned E[4] = {pack16(x[8] * sx, u), pack16(u, u), 0u, 0u};
+    const unsigned E[4] = {pack16(x[8] * sx, u), pack16(u * 0x1p-11f, u * 0x1p-22f), 0u, 0u};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const auto sw = __builtin_amdgcn_permlane32_swap(D[e], E[e], false, false);
@@ -301,7 +316,7 @@ __global__ __launch_bounds__(kAssignWaves * kWave, 1) void assign_large_kernel(c
     // operands of the staged entries, then (codebooks of at most kRowsMaxK entries) their fp32 rows
     __shared__ u32x4 s_a[kLargeLds / 16];
     __shared__ int s_next;       // the next unit to hand out
-    __shared__ unsigned s_max;   // the codebook's largest magnitude
+    __shared__ int s_max[kAssignWaves];  // the largest exponent of each wave's entries
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
@@ -319,13 +334,9 @@ __global__ __launch_bounds__(kAssignWaves * kWave, 1) void assign_large_kernel(c
     f32x4* const s_c = reinterpret_cast<f32x4*>(s_a + kpad * (kOperandLds / 16));
 
     // the codebook's scale: fp16 operands need it before any entry is staged
-    if (tid == 0) {
-        s_max = 0u;
-        s_next = ub + kAssignWaves;
-    }
+    if (tid == 0) s_next = ub + kAssignWaves;
     float xo[kDim];  // this lane's kernel
     load_kernel(L, ub + wave, lane, xo);
-    __syncthreads();
     float c0[kDim];  // entry tid, kept for the staging
     {
         unsigned m = 0u;
@@ -339,14 +350,35 @@ __global__ __launch_bounds__(kAssignWaves * kWave, 1) void assign_large_kernel(c
         for (int d = 0; d < kDim; ++d) m = max(m, __float_as_uint(c0[d]) & 0x7fffffffu);
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, off));
-        if (lane == 0) atomicMax(&s_max, m);
+        if (lane == 0) s_max[wave] = (int)(m >> 23);
     }
     __syncthreads();
-    const int Eraw = __builtin_amdgcn_readfirstlane((int)(s_max >> 23));
-    const int Ec = min(max(Eraw, 13), 254);
+    int Ec, Emax = 0, Emin = 255;  // of the waves whose entries are not all zero
+    {
+        const int E = lane < kAssignWaves ? s_max[lane] : 0;
+#pragma unroll
+        for (int w = 0; w < kAssignWaves; ++w) {
+            const int o = __builtin_amdgcn_readlane(E, w);
+            Emax = max(Emax, o);
+            Emin = min(Emin, o > 0 ? o : 255);
+        }
+        Ec = Emax;
+        if (Emax > Emin + kFarExp) {  // the middle one, and what lies within reach above it
+            int rank = 0, n = 0;
+            for (int w = 0; w < kAssignWaves; ++w) {
+                const int o = __builtin_amdgcn_readlane(E, w);
+                rank += o > 0 && (o < E || (o == E && w < lane)) ? 1 : 0;
+                n += o > 0 ? 1 : 0;
+            }
+            const unsigned long long mid = __ballot(E > 0 && rank == n / 2);  // one lane
+            Ec = min(Emax, __builtin_amdgcn_readlane(E, __ffsll((long long)mid) - 1) + kFarExp);
+        }
+        Ec = min(max(Ec, 13), 254);
+    }
     const float sc = scale_of(Ec), isc = inverse_of(Ec);
-    // the guard's terms of the codebook alone: 3 A and 2^(1 - 2a); never met when a value is not finite
-    const float gA = 3.0f * 0x1p-14f * isc, gN = Eraw == 255 ? __builtin_inff() : 2.0f * isc * isc;
+    // the guard's terms of the codebook alone: 3 A, 2^(-21 - 2a), and how far from zero far entries begin
+    const float gA = 3.0f * 0x1p-14f * isc, gN = 0x1p-21f * isc * isc;
+    const float gL = Emax > Ec ? 0.99f * kFarLength * isc : __builtin_inff();
 
     if (rows)
         stage16<true>(C, k, 0, kpad, sc, s_a, s_c, tid, c0);
@@ -415,7 +447,7 @@ __global__ __launch_bounds__(kAssignWaves * kWave, 1) void assign_large_kernel(c
             const float r = X1 + 1.01f * __builtin_amdgcn_sqrtf(rd) + 0x1p-60f;
             const float q = X1 + r, q2 = q * q;
             const float theta = 1.05f * (0x1p-9f * X1 * r + 0x1p-17f * q2 + 6.0f * 0x1p-14f * isx * r + gA * X1 + gN) + 0x1p-100f;
-            return valid && q2 < kTrustQ && m * isc * isx - (rd - xn2) > theta && rj < k;
+            return valid && q2 < kTrustQ && r < gL && m * isc * isx - (rd - xn2) > theta && rj < k;
         };
         rescore(s.m1, s.seg & 0xffffu, false);
         bool sure = guard(s.m2);

@@ -24,6 +24,20 @@ def host(t):
     return t.cpu().numpy()
 
 
+def best_us(f, reps=5):
+    f()
+    torch.cuda.synchronize()
+    best = np.inf
+    for _ in range(reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        b.synchronize()
+        best = min(best, 1e3 * a.elapsed_time(b))
+    return best
+
+
 def layer(n, k, seed):
     X = synth.laplace_layer(max(1, n // 64), 64, seed)
     X = np.ascontiguousarray(np.resize(X, (n, 9)) if X.shape[0] < n else X[:n])
@@ -121,6 +135,50 @@ def test_assign_extreme_values(k):
     check_assign(Z, C, "huge kernel")
 
 
+@pytest.mark.parametrize("k", [1500, 3000, 5000])
+def test_assign_with_far_entries(k):
+    """A few entries whose size would take the scale from the others: their exponents just below and
+    above where entries count as far, and at the ends of the range, kernels that lie at them, next to
+    them and midway, entries of zeros, and far entries only in one wave's part of the codebook."""
+    rng = np.random.default_rng(k)
+    X = laplace(1500, k)
+    C = synth.random_codebook_state(X, k, k)
+    top = float(2.0 ** np.floor(np.log2(np.abs(C).max())))
+    for name, sizes in [("edge", top * 2.0 ** np.arange(10, 16)), ("one step", [top * 4096 * 1.99, top * 8192 * 1.01]),
+                        ("huge", [1e10, 1e30, 3e38]), ("not finite", [np.inf, np.nan, 1e20]), ("tiny others", [1e25])]:
+        D, Y = C.copy(), X.copy()
+        if name == "tiny others":
+            D[:, :], Y = D * np.float32(1e-25), Y * np.float32(1e-25)
+        at = rng.integers(0, 64, len(sizes)) + 64 * rng.integers(0, 3)
+        for j, v in zip(at, sizes):
+            D[j] = np.float32(v) * rng.choice([-1.0, 1.0], 9).astype(np.float32)
+            if np.isfinite(v):
+                rows = rng.integers(0, 1500, 12)
+                Y[rows[:4]] = D[j] * np.float32(0.4)
+                Y[rows[4:8]] = D[j] * np.float32(0.6)
+                Y[rows[8:]] = D[j]
+        D[k // 2:k // 2 + 300] = 0
+        check_assign(Y, D, (k, name))
+
+
+@pytest.mark.parametrize("k", [1500, 4096])
+def test_assign_with_one_far_entry_takes_no_longer(k):
+    """(with the scale from the largest entry, whatever its size, up to ten times as long)"""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(k)
+    X = torch.randn(131072, 9, device=DEV, generator=g)
+    C = X[:k].clone()
+    plain = best_us(lambda: kq.kq_assign(X, C))
+    for v in (1e3, 1e4, 1e30, float("inf"), float("nan")):
+        D = C.clone()
+        D[k // 2] = v
+        us = best_us(lambda: kq.kq_assign(X, D))
+        assert us <= 1.6 * plain, (v, us, plain)
+    S = X * torch.exp(2 * torch.randn(131072, 1, device=DEV, generator=g))   # kernels of all sizes
+    us = best_us(lambda: kq.kq_assign(S, S[:k].clone()))
+    assert us <= 1.6 * plain, (us, plain)
+
+
 @pytest.mark.parametrize("bits", [2, 6])
 def test_wide_codebooks_share_their_launches(bits):
     """Codebooks of at least 16384 scalars of several sizes, some weights zero: together (the
@@ -197,20 +255,6 @@ def test_update_of_small_layers_with_a_frequent_entry(n, k, share):
             kq.kq_update_stack(st, distortion_from_assign=True, counts_only=counts_only)
             assert np.array_equal(host(st.counts[0]), np.bincount(idx, minlength=k)) and torch.equal(st.counts[0], z)
             assert np.array_equal(host(st.C[0]).view(np.uint32), host(Cn).view(np.uint32)), entry
-
-
-def best_us(f, reps=5):
-    f()
-    torch.cuda.synchronize()
-    best = np.inf
-    for _ in range(reps):
-        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        a.record()
-        f()
-        b.record()
-        b.synchronize()
-        best = min(best, 1e3 * a.elapsed_time(b))
-    return best
 
 
 def test_fit_of_a_small_layer_with_many_zero_kernels():
