@@ -396,26 +396,14 @@ __global__ __launch_bounds__(kAssignWaves * kWave, 1) void assign_kernel(const S
             if (L.best_d) L.best_d[i] = rd;
         }
 
-        // exact fp32 rescoring of the kernels the guard could not settle, one at a time
-        unsigned long long fl = __ballot(valid && !sure);
-        while (fl) {
-            const int f = __ffsll((long long)fl) - 1;
-            fl &= fl - 1;
-            float xf[kDim];  // lane f's kernel, the same in every lane (f is uniform)
-#pragma unroll
-            for (int d = 0; d < kDim; ++d)
-                xf[d] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x[d]), f));
-            float fd;
-            int fj;
-            scan_all(xf, k, lane, fd, fj, [&](float (&c)[kDim], int jj) { lds_row(c, s_c, jj); });
-            if (lane == f) {
-                if (fj == 0x7fffffff) fj = 0;  // every distance NaN or +inf: entry 0, as a plain scan gives
-                if (L.idx) L.idx[i] = fj;
-                if (L.best_d) L.best_d[i] = fd;
-                dist = fd;
-                myj = fj;
-            }
-        }
+        // exact fp32 rescoring of the kernels the guard could not settle
+        rescan(__ballot(valid && !sure), x, k, lane, [&](float (&c)[kDim], int jj) { lds_row(c, s_c, jj); },
+               [&](float fd, int fj) {
+                   if (L.idx) L.idx[i] = fj;
+                   if (L.best_d) L.best_d[i] = fd;
+                   dist = fd;
+                   myj = fj;
+               });
 
         if (FUSED && valid) {  // the update's exact member sums of this kernel, at the layer's shift
             atomicAdd(&s_cnt[myj], 1u);

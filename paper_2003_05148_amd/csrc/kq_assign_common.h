@@ -147,15 +147,18 @@ __device__ __forceinline__ AssignRun assign_run(const StackParams& p, int& n, in
     return run;
 }
 
-// exact fp32 rescoring of one kernel (xf, the same in every lane) over a whole codebook: each
+// exact fp32 rescoring of N kernels (xf, the same in every lane) over a whole codebook: each
 // lane scans entries lane, lane + 64, ... in increasing order (strict <: the lowest index among
-// equal distances), four rows in flight, then the lanes' (distance, index) pairs meet in their
+// equal distances), kU rows in flight, then the lanes' (distance, index) pairs meet in their
 // lexicographic minimum
-template <typename Row>
-__device__ __forceinline__ void scan_all(const float (&xf)[kDim], int k, int lane, float& fd, int& fj, Row&& row) {
+template <int N, typename Row>
+__device__ __forceinline__ void scan_all(const float (&xf)[N][kDim], int k, int lane, float (&fd)[N], int (&fj)[N], Row&& row) {
     constexpr int kU = 4;
-    fd = __builtin_inff();
-    fj = 0x7fffffff;
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+        fd[e] = __builtin_inff();
+        fj[e] = 0x7fffffff;
+    }
     for (int j0 = lane; j0 < k; j0 += kU * kWave) {
         float c[kU][kDim];
 #pragma unroll
@@ -163,13 +166,47 @@ __device__ __forceinline__ void scan_all(const float (&xf)[kDim], int k, int lan
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             const int jj = j0 + u * kWave;
-            const float d = sqdist9(xf, c[u]);
-            const bool take = jj < k && d < fd;
-            fj = take ? jj : fj;
-            fd = take ? d : fd;
+#pragma unroll
+            for (int e = 0; e < N; ++e) {
+                const float d = sqdist9(xf[e], c[u]);
+                const bool take = jj < k && d < fd[e];
+                fj[e] = take ? jj : fj[e];
+                fd[e] = take ? d : fd[e];
+            }
         }
     }
-    wave_argmin(fd, fj);
+#pragma unroll
+    for (int e = 0; e < N; ++e) wave_argmin(fd[e], fj[e]);
+}
+
+// The lanes of fl (their kernels x) rescored over the whole codebook, kMany at a time (the rows are read
+// once for them) while there are that many, then one by one; done(lane's distance, index) in each of them.
+// Where the screening cannot tell near ties apart (kernels of few dimensions, around a common offset, copies
+// of one entry), most kernels come here.  131,072 kernels, k = 4096, one by one and by four: of rank 2 610
+// and 283 us, around ten times their deviation 858 and 346, half of them zero with as many zero entries 542
+// and 247; none such 64 both.
+constexpr int kMany = 4;
+template <typename Row, typename Done>
+__device__ __forceinline__ void rescan(unsigned long long fl, const float (&x)[kDim], int k, int lane, Row&& row, Done&& done) {
+    auto some = [&](auto count) {
+        constexpr int N = decltype(count)::value;
+        int f[N];
+        float xf[N][kDim], fd[N];  // lane f's kernel, the same in every lane (f is uniform)
+        int fj[N];
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+            f[e] = __ffsll((long long)fl) - 1;
+            fl &= fl - 1;
+#pragma unroll
+            for (int d = 0; d < kDim; ++d) xf[e][d] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x[d]), f[e]));
+        }
+        scan_all<N>(xf, k, lane, fd, fj, row);
+#pragma unroll
+        for (int e = 0; e < N; ++e)
+            if (lane == f[e]) done(fd[e], fj[e] == 0x7fffffff ? 0 : fj[e]);  // every distance NaN or +inf: entry 0
+    };
+    while (__popcll(fl) >= kMany) some(std::integral_constant<int, kMany>{});
+    while (fl) some(std::integral_constant<int, 1>{});
 }
 
 }  // namespace kq

@@ -461,27 +461,17 @@ __global__ __launch_bounds__(kAssignWaves * kWave, 1) void assign_large_kernel(c
             if (L.idx) L.idx[i] = rj;  // (a fit's rounds before the last may keep no indices)
             if (L.best_d) L.best_d[i] = rd;
         }
-        // the kernels the guard could not settle, one at a time over the whole codebook
-        unsigned long long fl = __ballot(valid && !sure);
-        while (fl) {
-            const int f = __ffsll((long long)fl) - 1;
-            fl &= fl - 1;
-            float xf[kDim];  // lane f's kernel, the same in every lane (f is uniform)
-#pragma unroll
-            for (int d = 0; d < kDim; ++d) xf[d] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x[d]), f));
-            float fd;
-            int fj;
-            if (rows)
-                scan_all(xf, k, lane, fd, fj, [&](float (&c)[kDim], int jj) { lds_row(c, s_c, jj); });
-            else
-                scan_all(xf, k, lane, fd, fj, [&](float (&c)[kDim], int jj) { mem_row(c, C, jj); });
-            if (lane == f) {
-                if (fj == 0x7fffffff) fj = 0;  // every distance NaN or +inf: entry 0, as a plain scan gives
-                if (L.idx) L.idx[i] = fj;
-                if (L.best_d) L.best_d[i] = fd;
-                dist = fd;
-            }
-        }
+        // the kernels the guard could not settle, over the whole codebook
+        const unsigned long long fl = __ballot(valid && !sure);
+        auto done = [&](float fd, int fj) {
+            if (L.idx) L.idx[i] = fj;
+            if (L.best_d) L.best_d[i] = fd;
+            dist = fd;
+        };
+        if (rows)
+            rescan(fl, x, k, lane, [&](float (&c)[kDim], int jj) { lds_row(c, s_c, jj); }, done);
+        else
+            rescan(fl, x, k, lane, [&](float (&c)[kDim], int jj) { mem_row(c, C, jj); }, done);
         if (L.part) {
             const double v = wave_sum_f64(valid ? (double)dist : 0.0);
             if (lane == 0) L.part[lu] = v;

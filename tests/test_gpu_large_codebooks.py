@@ -233,6 +233,36 @@ def test_update_of_small_layers(shape):
             assert np.array_equal(host(gz), np.bincount(host(a), minlength=C.shape[0]))
 
 
+@pytest.mark.parametrize("k", [64, 200, 800, 1500, 3000, 5000])
+def test_rescans_of_any_number_of_kernels(k):
+    """Units of 64 kernels of which 0 to 64 are copies of an entry that the codebook holds twice: the
+    screening cannot settle those, and the lower index wins whether they are rescored by four or alone."""
+    rng = np.random.default_rng(k)
+    counts = [0, 1, 2, 3, 4, 5, 7, 8, 9, 63, 64, 30]
+    X = laplace(64 * len(counts) - 5, k)
+    C = synth.random_codebook_state(X, k, k)
+    pairs = rng.permutation(k)[:40].reshape(20, 2)
+    C[pairs[:, 1]] = C[pairs[:, 0]]
+    for u, c in enumerate(counts):
+        rows = 64 * u + rng.permutation(64 if u + 1 < len(counts) else 59)[:c]
+        X[rows] = C[pairs[rng.integers(0, 20, c), 0]]
+    check_assign(X, C, k)
+
+
+def test_assign_of_near_ties_by_four():
+    """Kernels around an offset of ten times their deviation: nearly all are rescored over the whole
+    codebook (one by one thirteen times as long as without the offset, by four five times)."""
+    k = 4096
+    g = torch.Generator(device=DEV)
+    g.manual_seed(k)
+    X = torch.randn(131072, 9, device=DEV, generator=g)
+    plain = best_us(lambda: kq.kq_assign(X, X[:k].clone()))
+    Y = X + 10.0
+    C = Y[:k].clone()
+    us = best_us(lambda: kq.kq_assign(Y, C))
+    assert us <= 8.0 * plain, (us, plain)
+
+
 # members of one workgroup's entries at the edge where a frequent entry is added in registers (3072)
 @pytest.mark.parametrize("n,k,share", [(3071, 200, 1.0), (3072, 200, 1.0), (3073, 200, 1.0), (16384, 300, 0.99), (16384, 300, 0.4),
                                        (16384, 300, 0.2), (12289, 4096, 0.9), (16000, 130, 0.7), (16384, 1024, 1.0)])
