@@ -119,20 +119,53 @@ def test_fc_quantizer_full_size_fc6_properties():
                 assert L[q] == np.float32(math.fsum(mem.tolist()) / mem.size), q
 
 
-@pytest.mark.parametrize("kind", ["normal", "integers", "tiny", "outliers"])
-def test_fc_threshold_path_equals_the_exact_search(kind):
-    """From 3 * 2^20 scalars on, codes come from per-level thresholds (a bucket table over
-    the data range, fp32 comparisons); with KQ_F_EXACT_SEARCH every code comes from the
-    exact fp64 search.  Both agree bit for bit, also on integer data (exact midpoints
-    between levels), on data whose tiny values make fp64 distances inexact (the thresholds
-    are then not used) and on data with a few far values, where most thresholds fall into
-    one bucket and are compared one by one."""
-    m = 9 * 932068                                            # 8,388,612 >= 3 * 2^20
-    vd = dev(data(kind, m, 77))
-    a = kq.kq_quantize_scalars(vd, 6, 30)
-    b = kq.kq_quantize_scalars(vd, 6, 30, search="exact")
+# Where v_hat goes decides who takes a large set: its own tensor gives room for the partitioned copy,
+# none ("absent") or v itself ("in place") leaves the coding launches, whose threshold form serves
+# sets from 3 * 2^20 scalars on
+def quantize_to(v, bits, iters, where, **kw):
+    if where == "own":
+        return kq.kq_quantize_scalars(v, bits, iters, **kw)
+    if where == "absent":
+        c, l, _, r = kq.kq_quantize_scalars(v, bits, iters, want_v_hat=False, **kw)
+        return c, l, l[c.long()], r
+    w = v.clone()
+    return kq.kq_quantize_scalars(w, bits, iters, v_hat=w, **kw)
+
+
+def same_as_exact(v, bits, iters, where, tag, **kw):
+    a = quantize_to(v, bits, iters, where, **kw)
+    b = kq.kq_quantize_scalars(v, bits, iters, search="exact")
     for x, y, name in zip(a, b, ["codes", "levels", "v_hat", "rounds"]):
-        assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), (kind, name)
+        assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), (tag, where, name)
+
+
+@pytest.mark.parametrize("where", ["own", "absent", "in place"])
+@pytest.mark.parametrize("kind", ["normal", "integers", "tiny", "outliers"])
+def test_fc_threshold_path_equals_the_exact_search(kind, where):
+    """From 3 * 2^20 scalars on, codes come from per-level thresholds (a bucket table over
+    the data range, fp32 comparisons), on the set partitioned by value or in the coding launches; with
+    KQ_F_EXACT_SEARCH every code comes from the exact fp64 search.  They agree bit for bit, also on
+    integer data (exact midpoints between levels), on data whose tiny values make fp64 distances inexact
+    and on data with a few far values, where most thresholds fall into one bucket and are compared one by
+    one."""
+    m = 9 * 932068                                            # 8,388,612 >= 3 * 2^20
+    same_as_exact(dev(data(kind, m, 77)), 6, 30, where, kind)
+
+
+@pytest.mark.parametrize("where", ["absent", "in place"])
+@pytest.mark.parametrize("bits", [1, 2, 3, 4, 5, 7, 8])
+def test_fc_threshold_coding_launches_of_other_widths(bits, where):
+    """(several steps of the grid, the last one ragged, and a set that begins off a 16-byte boundary)"""
+    v = dev(data("heavy", 4 * (512 * 1024 + 7) * 2 + 1, bits))
+    same_as_exact(v, bits, 6, where, bits)
+    same_as_exact(v[1:], bits, 6, where, bits)
+
+
+def test_fc_narrow_codes_of_a_large_set_with_v_hat():
+    """1 and 2 bits are never partitioned: thresholds in the coding launches, v_hat given."""
+    v = dev(data("heavy", 4 * (512 * 1024 + 7) * 2 + 3, 1))
+    for bits in (1, 2):
+        same_as_exact(v, bits, 30, "own", bits)
 
 
 @pytest.mark.parametrize("bits", [1, 2, 3, 6])
@@ -151,20 +184,19 @@ def test_fc_thresholds_with_values_far_below_the_levels(m, bits):
     check(np.concatenate([v, -v]), bits, 30, f"symmetric m={m} bits={bits}")
 
 
-@pytest.mark.parametrize("groups", [1, 5, 63, 65, 129, 600, 512 * 1024 + 7])
-def test_fc_threshold_rounds_with_a_partial_last_wave(groups):
+@pytest.mark.parametrize("where", ["own", "absent", "in place"])
+@pytest.mark.parametrize("groups", [1, 5, 63, 65, 129, 600, 512 * 1024 + 7, 2 * 512 * 1024 + 7])
+def test_fc_threshold_rounds_with_a_partial_last_wave(groups, where):
     """Sets whose last wave holds fewer than 64 groups of four scalars, with many codes changing
     there: every change must move its level's sums (the count of a wave's queued changes has to
-    agree in all its lanes, also in those past the end)."""
+    agree in all its lanes, also in those past the end).  The larger ones take one and two whole steps
+    of the coding launches' grid before (with a v_hat of their own they are partitioned instead)."""
     m = 4 * groups
     v = data("heavy", m, groups)
     v[-min(m, 256):] = np.random.default_rng(1).uniform(-0.02, 0.02, min(m, 256)).astype(np.float32)
     vd = dev(v)
     for iters in (1, 2, 3, 30):
-        a = kq.kq_quantize_scalars(vd, 6, iters, search="thresholds")
-        b = kq.kq_quantize_scalars(vd, 6, iters, search="exact")
-        for x, y, name in zip(a, b, ["codes", "levels", "v_hat", "rounds"]):
-            assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), (groups, iters, name)
+        same_as_exact(vd, 6, iters, where, (groups, iters), search="thresholds")
 
 
 @pytest.mark.parametrize("kind", ["symmetric", "late", "integers", "constant", "two", "heavy", "outliers", "tiny",

@@ -72,7 +72,7 @@ def test_stack_of_mixed_codebooks(shape):
 # sizes at the edges of the kernels' variants: 1024 | 1025 entries (three bf16 terms | one fp16
 # term), 1920 | 1921 (fp32 rows in LDS | in memory), 2048 | 2049 (segments of 256 | 512 entries),
 # 4864 | 4865 (resident | streamed), a last segment of one tile or one entry, and kernel counts
-# with several waves per unit, one wave per unit, and more units than a streaming wave keeps
+# with several waves per unit and one wave per unit (more units per wave: the next test)
 EDGES = [(1000, 1024), (1000, 1025), (64 * 300, 1025), (1000, 1920), (1000, 1921), (700, 2048), (700, 2049),
          (64 * 300 + 1, 2049), (500, 2561), (500, 4864), (500, 4865), (64 * 260, 4865), (300, 9217)]
 
@@ -95,6 +95,36 @@ def check_assign(X, C, tag):
 def test_assign_at_the_edges_of_the_variants(n, k):
     X = laplace(n, n + k)
     check_assign(X, synth.random_codebook_state(X, k, k), (n, k))
+
+
+@pytest.mark.parametrize("n,k", [(64 * 256 * 13 + 5, 1500), (64 * 256 * 13 + 5, 2303), (64 * 256 * 13 + 5, 4865),
+                                 (64 * 256 * 30 + 63, 4096), (64 * 256 * 97 + 1, 4865), (64 * 256 * 97 + 1, 9217)])
+def test_assign_of_many_units_per_workgroup(n, k):
+    """More than 12 units for a workgroup's 12 waves (the next unit handed out, its kernels loaded ahead; a
+    streaming wave's later units), and more than the 96 that streaming waves keep (the codebook streams
+    again).  The kernels repeat a block of 4099, so the oracle decides that block only."""
+    X = laplace(4099, n + k)
+    C = synth.random_codebook_state(X, k, k)
+    a = oracle.assign(X, C)
+    i = torch.arange(n, device=DEV) % 4099
+    idx, bd, J = kq.kq_assign(dev(X)[i], dev(C))
+    assert torch.equal(idx, dev(a["idx"]).to(torch.int32)[i])
+    assert torch.equal(bd, dev(a["d32"])[i])
+    Jr = float(a["d32"].astype(np.float64)[np.arange(n) % 4099].sum())
+    assert abs(float(host(J)[0]) - Jr) <= 1e-9 * Jr
+
+
+@pytest.mark.parametrize("n,k", [(4096, 60), (5000, 256), (20000, 512), (64 * 300 + 5, 1024)])
+def test_the_two_assignments_agree(n, k):
+    """A codebook of at most 1024 entries beside a larger one goes through the larger one's kernel: the
+    same indices and distances as alone, bit for bit, near ties among them."""
+    X, C = layer(n, k, 300 + k)
+    C[k // 2:k // 2 + 8] = np.nextafter(C[:8], np.float32(np.inf))
+    Y, D = layer(700, 1100, 5)
+    st = kq.Stack([dev(X), dev(Y)], [dev(C), dev(D)], best_d=True)
+    kq.kq_assign_stack(st)
+    idx, bd, _ = kq.kq_assign(dev(X), dev(C))
+    assert torch.equal(st.idx[0], idx) and torch.equal(st.best_d[0], bd)
 
 
 @pytest.mark.parametrize("k", [1500, 3000, 5000])
@@ -327,7 +357,9 @@ def test_assign_several_waves_per_unit(n, k):
     check_assign(X, C, (n, k, "copies"))
 
 
-@pytest.mark.parametrize("n,k", [(4095, 769), (4097, 1537), (8193, 7679), (40001, 2305)])
+# (the last three: chunks of several tiles of 4096 indices, the last tile ragged)
+@pytest.mark.parametrize("n,k", [(4095, 769), (4097, 1537), (8193, 7679), (40001, 2305), (262145, 4096), (300001, 7679),
+                                 (1048577, 2000)])
 def test_update_over_several_ranges(n, k):
     """The listed sums (no distortion asked for) and the sums in the order of the rows are the same
     integers: codebooks and counts bit for bit, with indices to ignore, an entry that holds every
