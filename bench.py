@@ -314,9 +314,7 @@ def main():
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / FP32_PEAK_TFLOPS,
                      "traffic": assign_traffic() if (args.config, k) == ("resnet18", 256) else None,
-                     "kernel": ("assign_kernel<true, 256> (member sums fused)" if fused else
-                                "assign_kernel<false, 1024>" if max(L.k for L in layers) <= 1024 else
-                                "assign_large_kernel")
+                     "kernel": assign_kernel_name(layers)
                                + f": one Lloyd round's launch per timed step (rounds 0..{min(args.steps, T) - 1}), "
                                  "whole stack per launch",
                      "pricing": "bf16-split (one fp16 product above 1024 entries) MFMA screening + exact fp32 "
@@ -326,6 +324,19 @@ def main():
     if not args.no_cpu_baseline:
         result["cpu_baseline"] = cpu_baseline(layers, C0, args.cpu_iters)
     print(json.dumps(result), flush=True)
+
+
+def assign_kernel_name(layers):
+    """The kernel of the fit's assignment launches for these layers (the library's rules)."""
+    ks, ns = [L.k for L in layers], [L.n for L in layers]
+    if max(ks) > 1024:
+        return "assign_large_kernel"
+    if max(ks) > 256:
+        return "assign_kernel<false, 1024, false>"
+    small = all(n <= 16384 and k > 128 and n <= 64 * k for n, k in zip(ns, ks))
+    if small and sum((n + 63) // 64 for n in ns) <= 1024:
+        return "assign_kernel<false, 1024, false> (one-launch update)"
+    return f"assign_kernel<true, 256, {'true' if min(ks) > 192 else 'false'}> (member sums fused)"
 
 
 def head_start(torch, stream, ms=2.0):

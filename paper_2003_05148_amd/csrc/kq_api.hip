@@ -61,8 +61,8 @@ int update_kernels(const kq_layer* layers, int32_t l0, int32_t l1) {
     };
     auto fit = [&](int target) {
         const int least = update_kernels_per_block(weighted, target);
-        for (int kpb = least; kpb <= 2 * (int64_t)least; kpb += kpb / 16 & ~255 ? kpb / 16 & ~255 : 256)
-            if (count(kpb) <= target) return kpb;
+        for (int64_t kpb = least; kpb <= 2 * (int64_t)least && kpb <= (1 << 30); kpb += std::max(kpb / 4096 * 256, int64_t(256)))
+            if (count((int)kpb) <= target) return (int)kpb;
         return least;
     };
     if (weighted >= kUpdateLongMin) {
@@ -181,8 +181,9 @@ bool fusable(const kq_layer* layers, int32_t l0, int32_t l1) {
 // has at most a few units, but stores a whole histogram for the finish to read.  It needs codebooks
 // of more than 128 entries (an update workgroup owns 16 of them) with at most 64 kernels per entry
 // (LDS atomics on the same sums), and runs short enough to share.  20 rounds, k = 256: 4096 kernels
-// 247 us fused, 231; 16384: 348, 303; 16 layers of 4096: 281, 270; but 8 layers of 16384: 292, 357,
-// and 4096 kernels at k = 100: 224, 239.
+// 241 us fused, 225; 16384: 356, 305; 16 layers of 4096: 281, 270; but 8 layers of 16384: 292, 357,
+// and 4096 kernels at k = 100: 224, 239.  With half of the kernels zero, one entry's, the fused sums
+// are the better ones: 4096 kernels 242 and 313, 16384: 355 and 432.
 bool fit_small(const kq_layer* layers, int32_t l0, int32_t l1) {
     int units = 0;
     for (int32_t l = l0; l < l1; ++l) {

@@ -291,7 +291,8 @@ __device__ __forceinline__ void stage(const float* __restrict__ C, int k, int kp
 }
 
 // FULL: every codebook of the launch has kFuseMaxK entries once padded (the pipelined scan; in one
-// kernel with the loop over any number of pairs it costs 16 registers and a spill)
+// kernel with the loop over any number of pairs it costs 16 registers and a spill).  It gives 0.3 % of a
+// pass of the ResNet-18 stack at k = 256 (1198 and 1195 us, runs of one side 0.1 % apart).
 template <bool FUSED, int KMAX, bool FULL>
 __global__ __launch_bounds__(kAssignWaves * kWave, 1) void assign_kernel(const StackParams p) {
     static_assert((!FUSED && !FULL) || KMAX == kFuseMaxK, "the sums' histogram holds kFuseMaxK entries");
@@ -509,9 +510,10 @@ __global__ __launch_bounds__(kSumThreads) void assign_finish_kernel(const StackP
 // A unit costs about kUnitCost + kpad entries' time: the scan grows with the codebook, the split,
 // the rescoring, the guard and the outputs do not (on the 16-layer ResNet-18 stack a fused launch
 // takes 22 us at k = 16 and 34 us at k = 256: 17 us without the start-up, and 12 us for 240
-// entries).  With units counted alike, the layers with the largest codebooks ended last: the
-// VGG-16 stack with k = 60 .. 1088 took 150 us per launch, with the cost 101 us; the ResNet-18
-// stack with k = 609 .. 7679 688 and 568 us.
+// entries).  With units counted alike, the layers with the largest codebooks ended last: this file's
+// kernel, when it still served them, took 150 us per launch on the VGG-16 stack with k = 60 .. 1088
+// and with the cost 101 us; on the ResNet-18 stack with k = 609 .. 7679 688 and 568 us.  The same cost
+// splits the grid of assign_large_kernel, for which it was not fitted.
 constexpr long long kUnitCost = 320;
 
 int assign_partition(const int* units, const int* ks, int nlayers, int* g) {

@@ -2,13 +2,17 @@
 // codebook of more than 1024 entries (kAssignMaxK).  The result is the one of kq_assign.hip, bit
 // for bit: the argmin of the fp32 squared distances, ties to the lowest index.
 //
-// With a large codebook the screening product is the work, and the matrix cores' power bounds it
-// (a pair of 32-entry tiles against 64 kernels: 115 ns on a SIMD with zeros for operands, 160 ns
-// with real ones; a large bf16 library product takes 222 ns for the same instructions).  So the
-// screening takes one fp16 product, K = 16, instead of the three bf16 cross terms, K = 32, of the
+// The screening takes one fp16 product, K = 16, instead of the three bf16 cross terms, K = 32, of the
 // small-codebook kernel, keeps the three best groups instead of two, and rescores a second group
-// where one is not enough.  The loop alone, with folding and real operands: 187 ns per pair with
-// K = 32, 112 ns with K = 16.
+// where one is not enough.  The product loop alone, with folding and real operands: 187 ns per pair of
+// 32-entry tiles, 64 kernels and SIMD with K = 32, 112 ns with K = 16.
+//
+// What bounds it: the issue of vector instructions (folding the scores, the three best, the fp32
+// rescoring).  By counters, on the VGG-16 stack with k = 60 .. 1088 (79 us a launch), the ResNet-18 stack
+// with k = 609 .. 7679 (315 us) and 1,048,576 kernels at k = 4096 (248 us): VALU busy 88, 75 and 79 % of a
+// SIMD's cycles, MFMA 18, 32 and 29 %, two thirds of these with a VALU instruction issued at the same
+// time; the address units 17, 32 and 50 % (the gathered rows of codebooks above 1920 entries).  The clock
+// is 1.8 to 2.0 GHz under this load.
 //
 // Screening.  Scaled by powers of two, ys = x 2^b and cs = c 2^a with max |c_jd| 2^a in [2^12,
 // 2^13) over the codebook but its far entries (kFarExp; they are scored as padding) and b = a, or less

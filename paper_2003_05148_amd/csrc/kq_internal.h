@@ -373,7 +373,8 @@ struct FcParams {
     int32_t* rounds_out;   // level updates made, or null
     long long m;
     int bits, iters;
-    int thr_mode;          // codes from thresholds: 0 from 2^23 scalars on, 1 never, 2 whenever valid
+    int thr_mode;          // codes from thresholds: 0 from kFcThresholdMin scalars on (partitioned from kFsMin on), 1 never,
+                           // 2 whenever valid
     float* minmax;         // [grid][2] per-workgroup min, max
     float* range;          // [4] the data's min, max; -; the bucket scale
     long long* part;       // [grid][levels][12] per-workgroup digits and counts

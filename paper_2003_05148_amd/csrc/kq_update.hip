@@ -117,7 +117,7 @@ __device__ __forceinline__ void add_rows(const UpdateCtx& c, const float* __rest
 // Whole passes, a row per thread and step before: the VGG-16 stack with k = 60 .. 1088 3452 us,
 // listed 3309; the ResNet-18 stack with k = 609 .. 7679 12.61 and 12.20 ms; 1,048,576 kernels, k =
 // 4096, 10 rounds 2918 and 2835 us.  Two barriers a tile and the gathers of 36-byte pieces bound it
-// (a launch on these stacks 24 and 53 us before, 16 and 34 with two workgroups per CU).
+// (a launch on these stacks 24 and 53 us before, now 16 and 31).
 constexpr int kTileBatch = 4;
 constexpr int kTileKernels = kTileBatch * kUpdateThreads;
 constexpr int kValueBatch = 8;  // values in flight per thread
@@ -254,7 +254,7 @@ constexpr int kFinishGroups = 6;
 constexpr int kFinishBatch = 9;
 constexpr int kFinishDirectWgs = 16;  // workgroups per layer in the direct form
 constexpr int kFinishDirectK = kFinishDirectWgs * kFinishEntries;  // 256
-constexpr int kFinishThreads = kFinishEntries * 10 * kFinishGroups;  // 640
+constexpr int kFinishThreads = kFinishEntries * 10 * kFinishGroups;  // 960
 static_assert(kFinishThreads >= kSumThreads, "the distortion sum uses the first kSumThreads threads");
 
 // GROUPS 6: six threads share a value's partials, 16 entries per workgroup.  GROUPS 1: one thread
