@@ -224,14 +224,14 @@ def _ws(device, nbytes):
     if torch.cuda.is_current_stream_capturing():
         return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
     pool = _scratch.__dict__
-    i = device.index if device.index is not None else torch.cuda.current_device()
-    key = (i, _stream(device))
+    key = (device.index, _stream(device))
     w = pool.get(key)
     if w is None:
         if len(pool) >= _MAX_SCRATCH:
             del pool[next(iter(pool))]  # the oldest
-        w = pool[key] = Workspace(torch.device("cuda", i))
-    return w.get(nbytes)
+        w = pool[key] = Workspace(device)
+    buf = w.buf
+    return buf if buf is not None and buf.numel() >= nbytes else w.get(nbytes)
 
 
 # ---- Sec. 3.1, Eq. (1) ---------------------------------------------------------------

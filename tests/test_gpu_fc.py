@@ -355,4 +355,4 @@ def test_fc_few_rounds_do_not_pay_for_a_partition(m, iters):
         assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), name
     auto = best_us(lambda: kq.kq_quantize_scalars(v, 6, iters, *a))
     exact = best_us(lambda: kq.kq_quantize_scalars(v, 6, iters, *b, search="exact"))
-    assert auto <= 1.3 * exact, (auto, exact)
+    assert auto <= 1.5 * exact, (auto, exact)

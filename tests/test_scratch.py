@@ -11,7 +11,7 @@ kq = pytest.importorskip("paper_2003_05148_amd")
 
 class Buffer:
     def __init__(self, device=None):
-        pass
+        self.buf = None
 
     def get(self, nbytes):
         return self
