@@ -1527,8 +1527,8 @@ hipError_t launch_fc_sets(const FcParams* sets, int n, hipStream_t s) {
 // Codes, and with them the end after a round that changed none, depend only on the cuts' counts:
 // {v < t} can only change when its size does.  Sums are exact integers, so levels are those of the
 // coding launches, bit for bit.  When a round's levels allow no thresholds (neighbours closer than
-// 2^-50 of the largest magnitude), this and the rounds after it code every scalar by a full scan
-// of the levels, in the same launches.
+// 2^-50 of the largest magnitude), this and the rounds after it code every scalar in full scans of
+// the set, in the same launches.
 // fc6's 102,760,448 scalars, 30 rounds: 4.43 -> 1.60 ms; 4,096,000: 0.87 -> 0.46 ms.
 constexpr int kFsBuckets = 1024;
 constexpr int kFsSample = 4 * kFsBuckets;
